@@ -51,7 +51,7 @@ template <int N> constexpr int py_of(int v) {
 template <int N> constexpr int pz_of(int v) {
     constexpr int P = Geo<N>::PPZ;
     if (!gs_tile_variants(N)) return P;
-    if (v == 1 && P >= 2) return P / 2;
+    if (v == 1 && P >= 2 && (P * Geo<N>::GZ) % 64 == 0) return P / 2;      // whole waves
     if (v == 2 && 4 * P * Geo<N>::AZ * 16 <= LDS_LIMIT && 4 * P * Geo<N>::GZ <= 1024) return 2 * P;
     return P;
 }

@@ -24,6 +24,12 @@
 
 #include <hip/hip_runtime.h>
 
+// Every product-sum below names its fused multiply-adds, and the compiler forms none of its
+// own: which products it would contract depends on the code around an inlined transform, and
+// the passes of one length have to compute the same bits in every kernel they are part of
+// (single evaluations, tile variants, the batched kernels).
+#pragma clang fp contract(off)
+
 namespace gsk {
 
 // Global-memory pointer.  Device functions take global data through this type so
@@ -42,13 +48,16 @@ __device__ __forceinline__ cpx cmk(double a, double b) {
 __device__ __forceinline__ cpx cadd(cpx a, cpx b) { return cmk(a.x + b.x, a.y + b.y); }
 __device__ __forceinline__ cpx csub(cpx a, cpx b) { return cmk(a.x - b.x, a.y - b.y); }
 __device__ __forceinline__ cpx cscale(cpx a, double s) { return cmk(a.x * s, a.y * s); }
+// s a + b
+__device__ __forceinline__ cpx caxpy(double s, cpx a, cpx b) { return cmk(fma(s, a.x, b.x), fma(s, a.y, b.y)); }
 __device__ __forceinline__ cpx cmul(cpx a, cpx b) {
-    return cmk(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
+    return cmk(fma(a.x, b.x, -(a.y * b.y)), fma(a.x, b.y, a.y * b.x));
 }
 // a * conj(b)
 __device__ __forceinline__ cpx cmulc(cpx a, cpx b) {
-    return cmk(a.x * b.x + a.y * b.y, a.y * b.x - a.x * b.y);
+    return cmk(fma(a.x, b.x, a.y * b.y), fma(a.y, b.x, -(a.x * b.y)));
 }
+__device__ __forceinline__ double cnorm(cpx a) { return fma(a.x, a.x, a.y * a.y); }
 __device__ __forceinline__ cpx cconj(cpx a) { return cmk(a.x, -a.y); }
 // a * (-i) for the forward sign, a * (+i) for the inverse one
 template <bool INV> __device__ __forceinline__ cpx mul_mi(cpx a) {
@@ -147,7 +156,7 @@ template <int E, int R, bool INV> __device__ __forceinline__ cpx twiddle_const(c
         constexpr CS w = unit_root(e, R);
         // forward: exp(-i theta) = c - i s; inverse: c + i s
         constexpr double s = INV ? w.s : -w.s;
-        return cmk(x.x * w.c - x.y * s, x.x * s + x.y * w.c);
+        return cmk(fma(x.x, w.c, -(x.y * s)), fma(x.x, s, x.y * w.c));
     }
 }
 
@@ -166,15 +175,14 @@ template <int S, bool INV> struct Dft<2, S, INV> {
 
 template <int S, bool INV> struct Dft<3, S, INV> {
     __device__ __forceinline__ static void run(cpx* v) {
-        constexpr double h = 0.86602540378443864676;   // sin(2 pi/3)
+        constexpr double h = INV ? -0.86602540378443864676 : 0.86602540378443864676;   // sin(2 pi/3)
         cpx a = v[0], b = v[S], c = v[2 * S];
         cpx t = cadd(b, c);
-        cpx m = cmk(a.x - 0.5 * t.x, a.y - 0.5 * t.y);
+        cpx m = cmk(fma(-0.5, t.x, a.x), fma(-0.5, t.y, a.y));
         cpx dd = csub(b, c);
-        cpx d = INV ? cmk(-h * dd.y, h * dd.x) : cmk(h * dd.y, -h * dd.x);
         v[0] = cadd(a, t);
-        v[S] = cadd(m, d);
-        v[2 * S] = csub(m, d);
+        v[S] = cmk(fma(h, dd.y, m.x), fma(-h, dd.x, m.y));
+        v[2 * S] = cmk(fma(-h, dd.y, m.x), fma(h, dd.x, m.y));
     }
 };
 
@@ -201,10 +209,9 @@ template <int S, bool INV> struct Dft<5, S, INV> {
         const cpx x0 = v[0];
         const cpx t1 = cadd(v[S], v[4 * S]), t3 = csub(v[S], v[4 * S]);
         const cpx t2 = cadd(v[2 * S], v[3 * S]), t4 = csub(v[2 * S], v[3 * S]);
-        const cpx a1 = cmk(x0.x + c1 * t1.x + c2 * t2.x, x0.y + c1 * t1.y + c2 * t2.y);
-        const cpx a2 = cmk(x0.x + c2 * t1.x + c1 * t2.x, x0.y + c2 * t1.y + c1 * t2.y);
-        const cpx b1 = mul_mi<INV>(cmk(s1 * t3.x + s2 * t4.x, s1 * t3.y + s2 * t4.y));
-        const cpx b2 = mul_mi<INV>(cmk(s2 * t3.x - s1 * t4.x, s2 * t3.y - s1 * t4.y));
+        const cpx a1 = caxpy(c2, t2, caxpy(c1, t1, x0)), a2 = caxpy(c1, t2, caxpy(c2, t1, x0));
+        const cpx b1 = mul_mi<INV>(caxpy(s2, t4, cscale(t3, s1)));
+        const cpx b2 = mul_mi<INV>(caxpy(-s1, t4, cscale(t3, s2)));
         v[0] = cadd(x0, cadd(t1, t2));
         v[S] = cadd(a1, b1);
         v[4 * S] = csub(a1, b1);
@@ -225,12 +232,12 @@ template <int S, bool INV> struct Dft<7, S, INV> {
         const cpx t2 = cadd(v[2 * S], v[5 * S]), d2 = csub(v[2 * S], v[5 * S]);
         const cpx t3 = cadd(v[3 * S], v[4 * S]), d3 = csub(v[3 * S], v[4 * S]);
         // cos(2 pi m k / 7) and sin(2 pi m k / 7) for k = 1, 2, 3 (mk reduced mod 7)
-        const cpx a1 = cmk(x0.x + c1 * t1.x + c2 * t2.x + c3 * t3.x, x0.y + c1 * t1.y + c2 * t2.y + c3 * t3.y);
-        const cpx a2 = cmk(x0.x + c2 * t1.x + c3 * t2.x + c1 * t3.x, x0.y + c2 * t1.y + c3 * t2.y + c1 * t3.y);
-        const cpx a3 = cmk(x0.x + c3 * t1.x + c1 * t2.x + c2 * t3.x, x0.y + c3 * t1.y + c1 * t2.y + c2 * t3.y);
-        const cpx b1 = mul_mi<INV>(cmk(s1 * d1.x + s2 * d2.x + s3 * d3.x, s1 * d1.y + s2 * d2.y + s3 * d3.y));
-        const cpx b2 = mul_mi<INV>(cmk(s2 * d1.x - s3 * d2.x - s1 * d3.x, s2 * d1.y - s3 * d2.y - s1 * d3.y));
-        const cpx b3 = mul_mi<INV>(cmk(s3 * d1.x - s1 * d2.x + s2 * d3.x, s3 * d1.y - s1 * d2.y + s2 * d3.y));
+        const cpx a1 = caxpy(c3, t3, caxpy(c2, t2, caxpy(c1, t1, x0)));
+        const cpx a2 = caxpy(c1, t3, caxpy(c3, t2, caxpy(c2, t1, x0)));
+        const cpx a3 = caxpy(c2, t3, caxpy(c1, t2, caxpy(c3, t1, x0)));
+        const cpx b1 = mul_mi<INV>(caxpy(s3, d3, caxpy(s2, d2, cscale(d1, s1))));
+        const cpx b2 = mul_mi<INV>(caxpy(-s1, d3, caxpy(-s3, d2, cscale(d1, s2))));
+        const cpx b3 = mul_mi<INV>(caxpy(s2, d3, caxpy(-s1, d2, cscale(d1, s3))));
         v[0] = cadd(x0, cadd(t1, cadd(t2, t3)));
         v[S] = cadd(a1, b1);
         v[6 * S] = csub(a1, b1);
@@ -288,6 +295,15 @@ template <int S, bool INV> struct Dft<10, S, INV> {
 template <int S, bool INV> struct Dft<14, S, INV> {
     __device__ __forceinline__ static void run(cpx* v) { DftComposite<2, 7, S, INV>::run(v); }
 };
+template <int S, bool INV> struct Dft<20, S, INV> {
+    __device__ __forceinline__ static void run(cpx* v) { DftComposite<4, 5, S, INV>::run(v); }
+};
+template <int S, bool INV> struct Dft<24, S, INV> {
+    __device__ __forceinline__ static void run(cpx* v) { DftComposite<4, 6, S, INV>::run(v); }
+};
+template <int S, bool INV> struct Dft<28, S, INV> {
+    __device__ __forceinline__ static void run(cpx* v) { DftComposite<4, 7, S, INV>::run(v); }
+};
 
 // ---------------------------------------------------------------------------
 // Transform plans: length N carried by G = N/E threads with E values each, the
@@ -308,11 +324,11 @@ template <> struct FftCfg<12> : FftPlan<12, 12, 2, 4, 3> {};
 template <> struct FftCfg<16> : FftPlan<16, 8, 2, 4, 4> {};
 template <> struct FftCfg<24> : FftPlan<24, 12, 2, 4, 6> {};
 template <> struct FftCfg<32> : FftPlan<32, 8, 2, 4, 8> {};
-template <> struct FftCfg<48> : FftPlan<48, 12, 3, 4, 4, 3> {};
+template <> struct FftCfg<48> : FftPlan<48, 12, 2, 12, 4> {};
 template <> struct FftCfg<64> : FftPlan<64, 8, 2, 8, 8> {};
-template <> struct FftCfg<96> : FftPlan<96, 12, 4, 4, 4, 2, 3> {};
+template <> struct FftCfg<96> : FftPlan<96, 12, 3, 4, 4, 6> {};
 template <> struct FftCfg<128> : FftPlan<128, 8, 3, 8, 4, 4> {};
-template <> struct FftCfg<192> : FftPlan<192, 12, 4, 4, 4, 4, 3> {};
+template <> struct FftCfg<192> : FftPlan<192, 12, 3, 4, 4, 12> {};
 template <> struct FftCfg<256> : FftPlan<256, 16, 2, 16, 16> {};
 template <> struct FftCfg<512> : FftPlan<512, 8, 3, 8, 8, 8> {};
 template <> struct FftCfg<1024> : FftPlan<1024, 16, 3, 16, 16, 4> {};
@@ -320,23 +336,33 @@ template <> struct FftCfg<2048> : FftPlan<2048, 16, 3, 16, 16, 8> {};
 // 3 * 2^7 and up (the transform grids of padding to B_3 at n = 256, 512, 1024)
 template <> struct FftCfg<384> : FftPlan<384, 12, 4, 4, 4, 4, 6> {};
 template <> struct FftCfg<768> : FftPlan<768, 12, 4, 4, 4, 4, 12> {};
-template <> struct FftCfg<1536> : FftPlan<1536, 24, 4, 8, 8, 8, 3> {};
+template <> struct FftCfg<1536> : FftPlan<1536, 24, 3, 8, 8, 24> {};
 // 5-smooth and 7-smooth lengths: 20 or 28 values per thread
-template <> struct FftCfg<20> : FftPlan<20, 20, 2, 4, 5> {};
+template <> struct FftCfg<20> : FftPlan<20, 20, 1, 20> {};
 template <> struct FftCfg<40> : FftPlan<40, 20, 2, 4, 10> {};
-template <> struct FftCfg<80> : FftPlan<80, 20, 3, 4, 4, 5> {};
+template <> struct FftCfg<80> : FftPlan<80, 20, 2, 20, 4> {};
 template <> struct FftCfg<160> : FftPlan<160, 20, 3, 4, 4, 10> {};
-template <> struct FftCfg<320> : FftPlan<320, 20, 4, 4, 4, 4, 5> {};
+template <> struct FftCfg<320> : FftPlan<320, 20, 3, 20, 4, 4> {};
 template <> struct FftCfg<640> : FftPlan<640, 20, 4, 4, 4, 4, 10> {};
-template <> struct FftCfg<28> : FftPlan<28, 28, 2, 4, 7> {};
+template <> struct FftCfg<28> : FftPlan<28, 28, 1, 28> {};
 template <> struct FftCfg<56> : FftPlan<56, 28, 2, 4, 14> {};
-template <> struct FftCfg<112> : FftPlan<112, 28, 3, 4, 4, 7> {};
+template <> struct FftCfg<112> : FftPlan<112, 28, 2, 28, 4> {};
 template <> struct FftCfg<224> : FftPlan<224, 28, 3, 4, 4, 14> {};
 
 // Plans for the fused spectrum pass, whose registers also hold the spectrum row:
 // fewer values per thread where that matters (n = 256: 8 values, radices 8, 8, 4,
 // a 32-thread transform, one LDS pad slot per 8 elements).
 template <int N> struct FftCfgFused : FftCfg<N> {};
+template <> struct FftCfgFused<48> : FftPlan<48, 12, 2, 4, 12> {};
+template <> struct FftCfgFused<80> : FftPlan<80, 20, 2, 4, 20> {};
+template <> struct FftCfgFused<128> : FftPlan<128, 8, 3, 8, 8, 2, 1, SLOTS_PAD8> {};
+template <> struct FftCfgFused<160> : FftPlan<160, 20, 3, 20, 4, 2, 1, SLOTS_PAD8> {};
+template <> struct FftCfgFused<192> : FftPlan<192, 12, 3, 4, 4, 12, 1, SLOTS_PAD8> {};
+template <> struct FftCfgFused<320> : FftPlan<320, 20, 4, 4, 4, 4, 5> {};
+template <> struct FftCfgFused<384> : FftPlan<384, 12, 4, 4, 4, 2, 12, SLOTS_PAD8> {};
+template <> struct FftCfgFused<512> : FftPlan<512, 8, 3, 8, 8, 8, 1, SLOTS_PAD8> {};
+template <> struct FftCfgFused<1536> : FftPlan<1536, 24, 3, 8, 8, 24, 1, SLOTS_PAD8> {};
+template <> struct FftCfgFused<2048> : FftPlan<2048, 16, 3, 16, 8, 16, 1, SLOTS_PAD8> {};
 template <> struct FftCfgFused<256> : FftPlan<256, 8, 3, 8, 8, 4, 1, SLOTS_PAD8> {};
 // n = 1024: 8 values per thread instead of 16 (no accumulator-register spills, two waves
 // per SIMD instead of one); measured 30.0 -> 26.4 ms for the 1024^3 fused pass and
@@ -415,19 +441,22 @@ template <class C> struct LdsAreaOf {
     static constexpr int size = (C::SLOTS == SLOTS_PAD8) ? C::N + C::N / 8 + 1 : LdsArea<C::N>::size;
 };
 
-// v[r S] *= w^r (conj for INV), r = 1..R-1, with w^{4a+c} = (w^4)^a w^c formed from
-// w1 = w and w4 = w^4: at most three multiplications deep.
+// v[r S] *= w^r (conj for INV), r = 1..R-1 (R <= 24), with w^{4a+c} = (w^4)^a w^c formed from
+// w1 = w and w4 = w^4: at most four multiplications deep.
 template <int R, int S, bool INV>
 __device__ __forceinline__ void mul_powers(cpx* v, cpx w1, cpx w4) {
+    static_assert(R <= 24, "powers of w4 formed up to the fifth");
     const cpx p2 = cmul(w1, w1);
     const cpx p3 = cmul(p2, w1);
     const cpx q2 = cmul(w4, w4);
     const cpx q3 = cmul(q2, w4);
+    const cpx q4 = cmul(q2, q2);
+    const cpx q5 = cmul(q2, q3);
 #pragma unroll
     for (int r = 1; r < R; ++r) {
         const int a = r / 4, c = r % 4;
         const cpx pc = c == 1 ? w1 : (c == 2 ? p2 : p3);
-        const cpx qa = a == 1 ? w4 : (a == 2 ? q2 : q3);
+        const cpx qa = a == 1 ? w4 : (a == 2 ? q2 : (a == 3 ? q3 : (a == 4 ? q4 : q5)));
         const cpx w = (a == 0) ? pc : (c == 0 ? qa : cmul(qa, pc));
         v[r * S] = INV ? cmulc(v[r * S], w) : cmul(v[r * S], w);
     }

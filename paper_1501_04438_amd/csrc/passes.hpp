@@ -74,12 +74,20 @@ __device__ __forceinline__ void swap_halves(cpx& a, cpx& b) {
     }
 }
 
+// Pencils per block of the fused pass: 128-thread blocks at the powers of two, one wave per
+// block at the other lengths, whose larger register blocks (12 to 28 values per thread) leave
+// a CU so few waves that whole-block granularity costs some of them.
+__host__ __device__ constexpr int ppz_of(int n, int gz) {
+    const int t = (n & (n - 1)) == 0 ? 128 : 64;
+    return 2 * gz >= t ? 1 : t / (2 * gz);
+}
+
 // Geometry of the fused pass on radix plan RV (FusedPlan): values and threads per
 // half-transform, LDS area, pencils per block.
 template <int N, int RV = 0> struct GeoZ {
     using FZ = FusedPlan<N, RV>;
     static constexpr int EZ = FZ::E, GZ = FZ::G, AZ = LdsAreaOf<FZ>::size;
-    static constexpr int PPZ = (2 * GZ >= 128) ? 1 : 128 / (2 * GZ);
+    static constexpr int PPZ = ppz_of(N, GZ);
     static constexpr int TZ = PPZ * 2 * GZ;
 };
 
@@ -93,9 +101,9 @@ template <int N> struct Geo {
     // runs instead of 32-byte ones; measured 0.069 -> 0.039 ms for the 2D x-inverse)
     static constexpr int PPX = (N <= 256) ? 8 : (N <= 512 ? 4 : 2);
     // P2/P4: z-pencils per block
-    static constexpr int PPY = (N <= 256) ? 16 : 8;
+    static constexpr int PPY = (N == 64 || N == 160 || N > 256) ? 8 : 16;
     // P3: pencils per block (two half-transforms each)
-    static constexpr int PPZ = (2 * GZ >= 128) ? 1 : 128 / (2 * GZ);
+    static constexpr int PPZ = ppz_of(N, GZ);
     static constexpr int TX = PPX * G, TY = PPY * G, TZ = PPZ * 2 * GZ;
 };
 
@@ -147,10 +155,10 @@ __device__ __forceinline__ void x_r2c_tile(gp<const double> __restrict__ rho, gp
     // transposed X1 side then fills whole 128-byte lines: P1 at 256^3 0.0765 -> 0.0706 ms),
     // else y0 + 2p and y0 + 2p + 1
     // (the pairing follows the default tile, Geo<N>::PPX pairs, for every PX: the same bits)
-    constexpr bool SPLIT = FULL && Gm::PPX % 8 == 0 && PP % 8 == 0;
+    constexpr bool SPLIT = FULL && Gm::PPX % 8 == 0 && N % (2 * Gm::PPX) == 0;
     constexpr int RS = SPLIT ? 8 : 1;
-    const int rowA = SPLIT ? y0 + 16 * (pA / 8) + pA % 8 : y0 + 2 * pA;
-    const int rowB = SPLIT ? y0 + 16 * (pB / 8) + pB % 8 : y0 + 2 * pB;
+    const int qA = bx * PP + pA, rowA = SPLIT ? 16 * (qA / 8) + qA % 8 : 2 * qA;
+    const int qB = bx * PP + pB, rowB = SPLIT ? 16 * (qB / 8) + qB % 8 : 2 * qB;
 
     cpx x[RL ? 1 : E];
     if constexpr (EMB) {
@@ -255,10 +263,10 @@ __device__ __forceinline__ void x_c2r_tile(gp<const cpx> __restrict__ X1, gp<dou
     // rows of pair p as in x_r2c_tile (8 rows apart in groups of 16 when the tile divides the
     // grid and holds a multiple of 8 pairs: whole 128-byte lines per load instruction on the
     // transposed X1 side)
-    constexpr bool SPLIT = FULL && Gm::PPX % 8 == 0 && PP % 8 == 0;
+    constexpr bool SPLIT = FULL && Gm::PPX % 8 == 0 && N % (2 * Gm::PPX) == 0;
     constexpr int RS = SPLIT ? 8 : 1;
-    const int rowA = SPLIT ? y0 + 16 * (pA / 8) + pA % 8 : y0 + 2 * pA;
-    const int rowB = SPLIT ? y0 + 16 * (pB / 8) + pB % 8 : y0 + 2 * pB;
+    const int qA = bx * PP + pA, rowA = SPLIT ? 16 * (qA / 8) + qA % 8 : 2 * qA;
+    const int qB = bx * PP + pB, rowB = SPLIT ? 16 * (qB / 8) + qB % 8 : 2 * qB;
     gp<const cpx> in = X1 + (size_t)z * (N + 1) * NY + rowB;
 
     cpx acc[E];
@@ -353,10 +361,10 @@ __device__ __forceinline__ void x_c2r_tile_split(gp<const cpx> __restrict__ X1, 
     const int y0 = bx * 2 * PP;
     constexpr bool FULL = (N % (2 * PP) == 0);
     const bool okA = active && (FULL || (y0 + 2 * pA) < N), okB = active && (FULL || (y0 + 2 * pB) < N);
-    constexpr bool SPLIT = FULL && Gm::PPX % 8 == 0 && PP % 8 == 0;
+    constexpr bool SPLIT = FULL && Gm::PPX % 8 == 0 && N % (2 * Gm::PPX) == 0;
     constexpr int RS = SPLIT ? 8 : 1;
-    const int rowA = SPLIT ? y0 + 16 * (pA / 8) + pA % 8 : y0 + 2 * pA;
-    const int rowB = SPLIT ? y0 + 16 * (pB / 8) + pB % 8 : y0 + 2 * pB;
+    const int qA = bx * PP + pA, rowA = SPLIT ? 16 * (qA / 8) + qA % 8 : 2 * qA;
+    const int qB = bx * PP + pB, rowB = SPLIT ? 16 * (qB / 8) + qB % 8 : 2 * qB;
     gp<const cpx> in = X1 + (size_t)z * (N + 1) * N + rowB;
     cpx v[E];
 #pragma unroll
@@ -719,22 +727,24 @@ __device__ __forceinline__ void fused_body(gp<cpx> __restrict__ X, gp<const cpx>
         const double ye = sy * dip.dxi[1];
         const double xo = (kx == NX) ? 0.0 : xe;
         const double yo = (ky == NY) ? 0.0 : ye;
+        // the pencil's part of the quadratic form, and the factor of its odd z terms
+        const double f0 = fma(dip.ccross[0] * xo, yo, fma(dip.cdiag[0] * xe, xe, dip.cdiag[1] * ye * ye));
+        const double fz = fma(dip.ccross[1], xo, dip.ccross[2] * yo);
 #pragma unroll
         for (int e = 0; e < E; ++e) {
             const int m = 2 * (t + G * e) + h;
             const int sz = m < N ? m : m - 2 * N;
             const double ze = sz * dip.dxi[2];
             const double zo = (m == N) ? 0.0 : ze;
-            const double f = dip.cdiag[0] * xe * xe + dip.cdiag[1] * ye * ye + dip.cdiag[2] * ze * ze +
-                             dip.ccross[0] * xo * yo + dip.ccross[1] * xo * zo + dip.ccross[2] * yo * zo;
-            const double s = f * sv[e] - dip.nm_over_M;
-            if constexpr (EN) acc += s * (v[e].x * v[e].x + v[e].y * v[e].y);
+            const double f = fma(zo, fz, fma(dip.cdiag[2] * ze, ze, f0));
+            const double s = fma(f, sv[e], -dip.nm_over_M);
+            if constexpr (EN) acc = fma(s, cnorm(v[e]), acc);
             v[e] = cscale(v[e], s);
         }
     } else {
 #pragma unroll
         for (int e = 0; e < E; ++e) {
-            if constexpr (EN) acc += sv[e] * (v[e].x * v[e].x + v[e].y * v[e].y);
+            if constexpr (EN) acc = fma(sv[e], cnorm(v[e]), acc);
             v[e] = cscale(v[e], sv[e]);
         }
     }
@@ -805,15 +815,15 @@ __device__ __forceinline__ void fused_body_pack(gp<cpx> __restrict__ X, gp<const
             const cpx b = cmk(0.5 * (v[e].x - w.x), 0.5 * (v[e].y + w.y));   // i B = (C - conj W) / 2
             const double sn = ldg<(NT & 4) != 0>(srow_n + (m <= N ? m : 2 * N - m));
             if constexpr (EN) {
-                acc += sv[e] * (a.x * a.x + a.y * a.y);
-                accn += sn * (b.x * b.x + b.y * b.y);
+                acc = fma(sv[e], cnorm(a), acc);
+                accn = fma(sn, cnorm(b), accn);
             }
             v[e] = cadd(cscale(a, sv[e]), cscale(b, sn));
         }
     } else {
 #pragma unroll
         for (int e = 0; e < E; ++e) {
-            if constexpr (EN) acc += sv[e] * (v[e].x * v[e].x + v[e].y * v[e].y);
+            if constexpr (EN) acc = fma(sv[e], cnorm(v[e]), acc);
             v[e] = cscale(v[e], sv[e]);
         }
     }
