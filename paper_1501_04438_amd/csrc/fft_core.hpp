@@ -319,11 +319,11 @@ struct FftPlan {
 
 // Default plans (few stages: one LDS exchange for n <= 256).
 template <int N> struct FftCfg;
-template <> struct FftCfg<8> : FftPlan<8, 8, 1, 8> {};
-template <> struct FftCfg<12> : FftPlan<12, 12, 2, 4, 3> {};
-template <> struct FftCfg<16> : FftPlan<16, 8, 2, 4, 4> {};
-template <> struct FftCfg<24> : FftPlan<24, 12, 2, 4, 6> {};
-template <> struct FftCfg<32> : FftPlan<32, 8, 2, 4, 8> {};
+template <> struct FftCfg<8> : FftPlan<8, 4, 2, 4, 2> {};
+template <> struct FftCfg<12> : FftPlan<12, 6, 2, 6, 2> {};
+template <> struct FftCfg<16> : FftPlan<16, 4, 2, 4, 4> {};
+template <> struct FftCfg<24> : FftPlan<24, 6, 3, 6, 2, 2> {};
+template <> struct FftCfg<32> : FftPlan<32, 4, 3, 4, 4, 2> {};
 template <> struct FftCfg<48> : FftPlan<48, 12, 2, 12, 4> {};
 template <> struct FftCfg<64> : FftPlan<64, 8, 2, 8, 8> {};
 template <> struct FftCfg<96> : FftPlan<96, 12, 3, 4, 4, 6> {};
@@ -338,14 +338,14 @@ template <> struct FftCfg<384> : FftPlan<384, 12, 4, 4, 4, 4, 6> {};
 template <> struct FftCfg<768> : FftPlan<768, 12, 4, 4, 4, 4, 12> {};
 template <> struct FftCfg<1536> : FftPlan<1536, 24, 3, 8, 8, 24> {};
 // 5-smooth and 7-smooth lengths: 20 or 28 values per thread
-template <> struct FftCfg<20> : FftPlan<20, 20, 1, 20> {};
-template <> struct FftCfg<40> : FftPlan<40, 20, 2, 4, 10> {};
+template <> struct FftCfg<20> : FftPlan<20, 10, 2, 10, 2> {};
+template <> struct FftCfg<40> : FftPlan<40, 10, 3, 10, 2, 2> {};
 template <> struct FftCfg<80> : FftPlan<80, 20, 2, 20, 4> {};
 template <> struct FftCfg<160> : FftPlan<160, 20, 3, 4, 4, 10> {};
 template <> struct FftCfg<320> : FftPlan<320, 20, 3, 20, 4, 4> {};
 template <> struct FftCfg<640> : FftPlan<640, 20, 4, 4, 4, 4, 10> {};
-template <> struct FftCfg<28> : FftPlan<28, 28, 1, 28> {};
-template <> struct FftCfg<56> : FftPlan<56, 28, 2, 4, 14> {};
+template <> struct FftCfg<28> : FftPlan<28, 14, 2, 14, 2> {};
+template <> struct FftCfg<56> : FftPlan<56, 14, 3, 14, 2, 2> {};
 template <> struct FftCfg<112> : FftPlan<112, 28, 2, 28, 4> {};
 template <> struct FftCfg<224> : FftPlan<224, 28, 3, 4, 4, 14> {};
 
@@ -355,6 +355,7 @@ template <> struct FftCfg<224> : FftPlan<224, 28, 3, 4, 4, 14> {};
 template <int N> struct FftCfgFused : FftCfg<N> {};
 template <> struct FftCfgFused<48> : FftPlan<48, 12, 2, 4, 12> {};
 template <> struct FftCfgFused<80> : FftPlan<80, 20, 2, 4, 20> {};
+template <> struct FftCfgFused<112> : FftPlan<112, 28, 2, 28, 4, 1, 1, SLOTS_PAD8> {};
 template <> struct FftCfgFused<128> : FftPlan<128, 8, 3, 8, 8, 2, 1, SLOTS_PAD8> {};
 template <> struct FftCfgFused<160> : FftPlan<160, 20, 3, 20, 4, 2, 1, SLOTS_PAD8> {};
 template <> struct FftCfgFused<192> : FftPlan<192, 12, 3, 4, 4, 12, 1, SLOTS_PAD8> {};
