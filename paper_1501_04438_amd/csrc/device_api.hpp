@@ -82,6 +82,11 @@ hipError_t launch_energy_total(double* part, int count, double scale, double* en
 // slab given in the arguments (a whole evaluation when the slab covers kx = 0..n).  A grid
 // whose extents nx, ny (, nz) differ runs each pass at the length of the axis it transforms.
 hipError_t launch_eval(const EvalArgs& a, hipStream_t s, int which = -1);
+// Launches in place of passes 2 to 5 on the cubic 3D grids plane_fused() names: every kx plane
+// through passes 2 to 4 in one block, its result left as two halves in X2 (which holds every
+// plane), and the x-inverse pass on their sum.
+constexpr int PASS_PLANE = 6, PASS_X_INVERSE_HALVES = 7;
+bool plane_fused(int n);
 bool eval_size_supported(int d, int n);
 // Tile variants compiled for length n: bit 0 x double, 1 y half, 2 y double, 3 fused half,
 // 4 fused double.

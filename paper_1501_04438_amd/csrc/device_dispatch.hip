@@ -11,6 +11,7 @@ namespace gsk {
 #define GS_DECL(N)                                                   \
     hipError_t launch_eval_##N(const EvalArgs&, hipStream_t, int);   \
     hipError_t launch_eval_g_##N(const EvalArgs&, hipStream_t, int); \
+    bool plane_fused_##N();                                          \
     int tile_variants_##N();
 GS_SIZE_LIST(GS_DECL)
 #undef GS_DECL
@@ -143,6 +144,16 @@ hipError_t launch_eval(const EvalArgs& a, hipStream_t s, int which) {
         GS_SIZE_LIST(GS_CASE)
 #undef GS_CASE
         default: return hipErrorInvalidValue;
+    }
+}
+
+bool plane_fused(int n) {
+    switch (n) {
+#define GS_CASE(N) \
+    case N: return plane_fused_##N();
+        GS_SIZE_LIST(GS_CASE)
+#undef GS_CASE
+        default: return false;
     }
 }
 

@@ -58,20 +58,20 @@ template <int N> constexpr int pz_of(int v) {
 
 // P5 with row pairs PX per block on radix plan XV; with the energy, the total of the fused
 // pass's pencil sums.
-template <int PX, int XV = 0>
+template <int PX, int XV = 0, bool HV = false>
 static hipError_t launch_x_inverse_v(const EvalArgs& a, hipStream_t s) {
     constexpr int N = GS_N;
     constexpr int T = p5_threads<N, PX, XV>();
-    const cpx* const X1 = reinterpret_cast<const cpx*>(a.X1);
+    const cpx* const X1 = reinterpret_cast<const cpx*>(HV ? a.X2 : a.X1);
     const cpx* const tw = reinterpret_cast<const cpx*>(a.tw);
     const bool hint = (a.hint_bits >> 4) & 1;
     const dim3 gx((N + 2 * PX - 1) / (2 * PX), a.d == 3 ? N : 1);
     if (a.energy && a.oscale != 1.0) {
-        if (hint) k_x_c2r<N, NT_P5, PX, true, XV><<<gx, T, 0, s>>>(X1, a.u, tw, a.oscale);
-        else k_x_c2r<N, 0, PX, true, XV><<<gx, T, 0, s>>>(X1, a.u, tw, a.oscale);
+        if (hint) k_x_c2r<N, NT_P5, PX, true, XV, HV><<<gx, T, 0, s>>>(X1, a.u, tw, a.oscale);
+        else k_x_c2r<N, 0, PX, true, XV, HV><<<gx, T, 0, s>>>(X1, a.u, tw, a.oscale);
     } else {
-        if (hint) k_x_c2r<N, NT_P5, PX, false, XV><<<gx, T, 0, s>>>(X1, a.u, tw);
-        else k_x_c2r<N, 0, PX, false, XV><<<gx, T, 0, s>>>(X1, a.u, tw);
+        if (hint) k_x_c2r<N, NT_P5, PX, false, XV, HV><<<gx, T, 0, s>>>(X1, a.u, tw);
+        else k_x_c2r<N, 0, PX, false, XV, HV><<<gx, T, 0, s>>>(X1, a.u, tw);
     }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || !a.energy) return e;
@@ -81,6 +81,7 @@ static hipError_t launch_x_inverse_v(const EvalArgs& a, hipStream_t s) {
 
 // Padding to B_3 on a cubic transform grid (lengths 3n/2): P1 and P5 with the density and the
 // potential at their own extents (a.px, a.py, a.pz), at the default tile.
+template <bool HV = false>
 static hipError_t launch_x_emb(const EvalArgs& a, hipStream_t s, int pass) {
     constexpr int N = GS_N;
     if constexpr (N % 3 == 0) {
@@ -98,7 +99,7 @@ static hipError_t launch_x_emb(const EvalArgs& a, hipStream_t s, int pass) {
             else k_x_r2c_emb<N, 0><<<gx, Gm::TX, 0, s>>>(a.rho, X1, tw, ext);
             return hipGetLastError();
         }
-        const cpx* const X1 = reinterpret_cast<const cpx*>(a.X1);
+        const cpx* const X1 = reinterpret_cast<const cpx*>(HV ? a.X2 : a.X1);
         constexpr int T = p5_threads<N, Gm::PPX>();
         const bool hint = (a.hint_bits >> 4) & 1;
         // the x-inverse pass only for the rows and planes that hold potential values
@@ -106,11 +107,11 @@ static hipError_t launch_x_emb(const EvalArgs& a, hipStream_t s, int pass) {
         gx.y = ext.nz;
         const bool sc = a.energy && a.oscale != 1.0;
         if (sc) {
-            if (hint) k_x_c2r_emb<N, NT_P5, true><<<gx, T, 0, s>>>(X1, a.u, tw, ext, a.oscale);
-            else k_x_c2r_emb<N, 0, true><<<gx, T, 0, s>>>(X1, a.u, tw, ext, a.oscale);
+            if (hint) k_x_c2r_emb<N, NT_P5, true, HV><<<gx, T, 0, s>>>(X1, a.u, tw, ext, a.oscale);
+            else k_x_c2r_emb<N, 0, true, HV><<<gx, T, 0, s>>>(X1, a.u, tw, ext, a.oscale);
         } else {
-            if (hint) k_x_c2r_emb<N, NT_P5, false><<<gx, T, 0, s>>>(X1, a.u, tw, ext, 1.0);
-            else k_x_c2r_emb<N, 0, false><<<gx, T, 0, s>>>(X1, a.u, tw, ext, 1.0);
+            if (hint) k_x_c2r_emb<N, NT_P5, false, HV><<<gx, T, 0, s>>>(X1, a.u, tw, ext, 1.0);
+            else k_x_c2r_emb<N, 0, false, HV><<<gx, T, 0, s>>>(X1, a.u, tw, ext, 1.0);
         }
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess || !a.energy) return e;
@@ -264,6 +265,40 @@ static hipError_t launch_fused(const EvalArgs& a, hipStream_t s, const DipoleArg
     return launch_fused_v<pz_of<N>(0)>(a, s, dip);
 }
 
+// P2 to P4 of a small 3D grid in one launch (k_plane, one block per kx plane and parity of ky),
+// its two halves left in X2; and the x-inverse pass on those.
+static hipError_t launch_plane(const EvalArgs& a, hipStream_t s, const DipoleArgs& dip, int which) {
+    constexpr int N = GS_N;
+    if constexpr (plane_fused<N>()) {
+        if (which == PASS_X_INVERSE_HALVES) {
+            if (a.emb) return launch_x_emb<true>(a, s, 5);
+            return launch_x_inverse_v<px_of<N>(0), 0, true>(a, s);
+        }
+        const cpx* const X1 = reinterpret_cast<const cpx*>(a.X1);
+        cpx* const H = reinterpret_cast<cpx*>(a.X2);
+        const cpx* const tw = reinterpret_cast<const cpx*>(a.tw);
+        const int zs = a.emb ? a.pz : N;
+        constexpr unsigned nb = 2 * (N + 1);
+        constexpr int T = GeoP<N>::T;
+        if (a.dipolar) {
+            if (a.energy) k_plane<N, SPEC_DIPOLAR, true><<<nb, T, 0, s>>>(X1, H, a.spec, tw, dip, zs, a.epart);
+            else k_plane<N, SPEC_DIPOLAR, false><<<nb, T, 0, s>>>(X1, H, a.spec, tw, dip, zs, nullptr);
+        } else {
+            if (a.energy) k_plane<N, SPEC_PLAIN, true><<<nb, T, 0, s>>>(X1, H, a.spec, tw, dip, zs, a.epart);
+            else k_plane<N, SPEC_PLAIN, false><<<nb, T, 0, s>>>(X1, H, a.spec, tw, dip, zs, nullptr);
+        }
+        return hipGetLastError();
+    } else {
+        (void)a;
+        (void)s;
+        (void)dip;
+        (void)which;
+        return hipErrorInvalidValue;
+    }
+}
+
+bool GS_CAT(plane_fused_, GS_N)() { return plane_fused<GS_N>(); }
+
 int GS_CAT(tile_variants_, GS_N)() {
     // bit 0: an x variant exists (either x pass); bits 1, 2: y half / double; bits 3, 4: fused
     // half / double; bit 5: a radix-plan variant of the fused pass; bit 6: of the x passes;
@@ -376,6 +411,7 @@ hipError_t GS_CAT(launch_eval_, GS_N)(const EvalArgs& a, hipStream_t s, int whic
         dip.ccross[i] = a.ccross[i];
     }
     dip.nm_over_M = a.nm_over_M;
+    if (which >= PASS_PLANE) return launch_plane(a, s, dip, which);
     auto run = [&](int p) { return which < 0 || which == p; };
     hipError_t e = hipSuccess;
     if (run(1) && (e = launch_x_forward(a, s)) != hipSuccess) return e;

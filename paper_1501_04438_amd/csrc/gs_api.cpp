@@ -284,6 +284,21 @@ static hipError_t run_step(gs_plan p, gsk::EvalArgs& a, int step, hipStream_t s)
     return e;
 }
 
+// A whole evaluation on stream s, in order.  Small cubic 3D grids run the three middle steps as
+// one launch per evaluation (gsk::PASS_PLANE; the same bits) when X2 holds every plane.
+static hipError_t run_steps(gs_plan p, gsk::EvalArgs& a, hipStream_t s) {
+    const int last = (int)p->steps.size() - 1;
+    hipError_t e = hipSuccess;
+    if (p->d == 3 && p->cube && p->nslabs == 1 && p->x2_planes == p->nk[0] + 1 && gsk::plane_fused(p->nf)) {
+        e = run_step(p, a, 0, s);
+        if (e == hipSuccess) e = gsk::launch_eval(a, s, gsk::PASS_PLANE);
+        if (e == hipSuccess) e = gsk::launch_eval(a, s, gsk::PASS_X_INVERSE_HALVES);
+        return e;
+    }
+    for (int i = 0; i <= last && e == hipSuccess; ++i) e = run_step(p, a, i, s);
+    return e;
+}
+
 // The slab chains (y-forward, fused, y-inverse of one kx slab) on p->nstreams streams:
 // forked from the plan's stream after the x pass, joined before the x-inverse pass.
 static hipError_t run_concurrent(gs_plan p, gsk::EvalArgs& a) {
@@ -341,7 +356,7 @@ gs_status eval_chain(gs_plan p, const double* in, double* out, int step, double*
     } else if (p->d == 3 && p->nstreams > 1 && p->nslabs > 1) {
         e = run_concurrent(p, a);
     } else {
-        for (int i = 0; i < (int)p->steps.size() && e == hipSuccess; ++i) e = run_step(p, a, i, p->stream);
+        e = run_steps(p, a, p->stream);
     }
     if (e != hipSuccess) return hip_fail(e, "evaluation launch");
     return GS_OK;
@@ -375,8 +390,7 @@ gs_status eval_chain_ws(gs_plan p, const double* in, double* out, double2* ws) {
     }
     DeviceScope ds(p->device);
     if (ds.err != hipSuccess) return hip_fail(ds.err, "hipSetDevice");
-    hipError_t e = hipSuccess;
-    for (int i = 0; i < (int)p->steps.size() && e == hipSuccess; ++i) e = run_step(p, a, i, p->stream);
+    const hipError_t e = run_steps(p, a, p->stream);
     if (e != hipSuccess) return hip_fail(e, "evaluation launch");
     return GS_OK;
 }

@@ -245,8 +245,9 @@ k_x_r2c(const double* __restrict__ rho, cpx* __restrict__ X1,
 // SC: the outputs are stored times oscale (the rho gradient of the energy, cell u).
 // EMB (with CUBE): the potential is stored for the first ext.nx x ext.ny x ext.nz points of the
 // transform grid only, into an array of those extents (padding to B_3 without a copy).
+// HV (with CUBE): X1 holds two halves whose sum is the input (x_c2r_tile_split).
 template <int N, int NT = NT_P5, bool SC = false, bool CUBE = true, int PX = Geo<N>::PPX, int XV = 0,
-          bool EMB = false>
+          bool EMB = false, bool HV = false>
 __device__ __forceinline__ void x_c2r_tile(gp<const cpx> __restrict__ X1, gp<double> u,
                                            gp<const cpx> __restrict__ tw, int bx, int z, int tid, bool active,
                                            cpx* lds, Ext ext = Ext(), double oscale = 1.0) {
@@ -285,6 +286,10 @@ __device__ __forceinline__ void x_c2r_tile(gp<const cpx> __restrict__ X1, gp<dou
                 gp<const cpx> p = in + (size_t)mm * NY;
                 a = ldg<NT & 1>(p);
                 b = ldg<NT & 1>(p + RS);
+                if constexpr (HV) {
+                    a = cadd(a, ldg<NT & 1>(p + (size_t)(N + 1) * N * N));
+                    b = cadd(b, ldg<NT & 1>(p + (size_t)(N + 1) * N * N + RS));
+                }
             }
             if (!direct) { a.y = -a.y; b.y = -b.y; }
             v[e] = cmk(a.x - b.y, a.y + b.x);          // a + i b
@@ -346,7 +351,9 @@ template <int N, int PX, int XV = 0> constexpr int p5_threads() {
     return (p5_split<N, PX, XV>() ? 2 : 1) * PX * GeoX<N, XV>::G;
 }
 
-template <int N, int NT, bool SC, int PX, int XV = 0, bool EMB = false>
+// HV: X1 holds the two halves k_plane leaves (the second one (N + 1) N N values on), whose sum
+// is the transform's input.
+template <int N, int NT, bool SC, int PX, int XV = 0, bool EMB = false, bool HV = false>
 __device__ __forceinline__ void x_c2r_tile_split(gp<const cpx> __restrict__ X1, gp<double> u,
                                                  gp<const cpx> __restrict__ tw, int bx, int z, int tid, cpx* lds,
                                                  double oscale, bool active = true, Ext ext = Ext()) {
@@ -377,6 +384,10 @@ __device__ __forceinline__ void x_c2r_tile_split(gp<const cpx> __restrict__ X1, 
             gp<const cpx> p = in + (size_t)mm * N;
             a = ldg<NT & 1>(p);
             b = ldg<NT & 1>(p + RS);
+            if constexpr (HV) {
+                a = cadd(a, ldg<NT & 1>(p + (size_t)(N + 1) * N * N));
+                b = cadd(b, ldg<NT & 1>(p + (size_t)(N + 1) * N * N + RS));
+            }
         }
         if (!direct) { a.y = -a.y; b.y = -b.y; }
         v[e] = cmk(a.x - b.y, a.y + b.x);              // a + i b
@@ -404,16 +415,16 @@ __device__ __forceinline__ void x_c2r_tile_split(gp<const cpx> __restrict__ X1, 
 
 // P5; SC: the outputs stored times oscale (the energy's rho gradient cell u; the energy
 // itself is summed by the fused pass).
-template <int N, int NT = NT_P5, int PX = Geo<N>::PPX, bool SC = false, int XV = 0>
+template <int N, int NT = NT_P5, int PX = Geo<N>::PPX, bool SC = false, int XV = 0, bool HV = false>
 __global__ void __launch_bounds__((p5_threads<N, PX, XV>())) k_x_c2r(const cpx* __restrict__ X1, double* __restrict__ u,
                                                                    const cpx* __restrict__ tw, double oscale = 1.0) {
     if constexpr (p5_split<N, PX, XV>()) {
         __shared__ cpx lds[2 * PX * Geo<N>::A];
-        x_c2r_tile_split<N, NT, SC, PX, XV>((gp<const cpx>)X1, (gp<double>)u, (gp<const cpx>)tw, blockIdx.x,
+        x_c2r_tile_split<N, NT, SC, PX, XV, false, HV>((gp<const cpx>)X1, (gp<double>)u, (gp<const cpx>)tw, blockIdx.x,
                                             blockIdx.y, threadIdx.x, lds, oscale);
     } else {
         __shared__ cpx lds[PX * Geo<N>::A];
-        x_c2r_tile<N, NT, SC, true, PX, XV>((gp<const cpx>)X1, (gp<double>)u, (gp<const cpx>)tw, blockIdx.x,
+        x_c2r_tile<N, NT, SC, true, PX, XV, false, HV>((gp<const cpx>)X1, (gp<double>)u, (gp<const cpx>)tw, blockIdx.x,
                                             blockIdx.y, threadIdx.x, true, lds, Ext(), oscale);
     }
 }
@@ -429,7 +440,7 @@ k_x_r2c_emb(const double* __restrict__ rho, cpx* __restrict__ X1, const cpx* __r
                                                          blockIdx.x, blockIdx.y, threadIdx.x, true, lds, ext);
 }
 
-template <int N, int NT, bool SC>
+template <int N, int NT, bool SC, bool HV = false>
 __global__ void __launch_bounds__((p5_threads<N, Geo<N>::PPX>())) k_x_c2r_emb(const cpx* __restrict__ X1,
                                                                               double* __restrict__ u,
                                                                               const cpx* __restrict__ tw, Ext ext,
@@ -437,11 +448,11 @@ __global__ void __launch_bounds__((p5_threads<N, Geo<N>::PPX>())) k_x_c2r_emb(co
     constexpr int PX = Geo<N>::PPX;
     if constexpr (p5_split<N, PX>()) {
         __shared__ cpx lds[2 * PX * Geo<N>::A];
-        x_c2r_tile_split<N, NT, SC, PX, 0, true>((gp<const cpx>)X1, (gp<double>)u, (gp<const cpx>)tw, blockIdx.x,
+        x_c2r_tile_split<N, NT, SC, PX, 0, true, HV>((gp<const cpx>)X1, (gp<double>)u, (gp<const cpx>)tw, blockIdx.x,
                                                  blockIdx.y, threadIdx.x, lds, oscale, true, ext);
     } else {
         __shared__ cpx lds[PX * Geo<N>::A];
-        x_c2r_tile<N, NT, SC, true, PX, 0, true>((gp<const cpx>)X1, (gp<double>)u, (gp<const cpx>)tw, blockIdx.x,
+        x_c2r_tile<N, NT, SC, true, PX, 0, true, HV>((gp<const cpx>)X1, (gp<double>)u, (gp<const cpx>)tw, blockIdx.x,
                                                  blockIdx.y, threadIdx.x, true, lds, ext, oscale);
     }
 }
@@ -702,18 +713,18 @@ __device__ __forceinline__ void fused_energy_store(double acc, bool ok, int penc
     }
 }
 
-// Transform, spectrum multiplication, inverse transform and even/odd combination
-// of one pencil held in v (spectrum values in sv); stores the pencil if ok.  EN: also the
-// pencil's energy sum into part (fused_energy_store).
-template <int N, int DIM, int MODE, int NT = NT_P3, bool EN = false, int RV = 0>
-__device__ __forceinline__ void fused_body(gp<cpx> __restrict__ X, gp<const cpx> __restrict__ tw, int pencil, int kx0,
-                                           bool ok, const DipoleArgs& dip, int t, int h, int pl,
-                                           cpx (&v)[GeoZ<N, RV>::EZ], const double (&sv)[GeoZ<N, RV>::EZ],
-                                           cpx* lds, cpx* area, int NX, int NY, gp<double> part = nullptr) {
+// Transform, spectrum multiplication and inverse transform of one pencil's halves held in v
+// (spectrum values in sv); on exit every half holds its share of the cropped result, to be
+// added to the other half's.  EN: also the pencil's energy sum into part (fused_energy_store).
+template <int N, int DIM, int MODE, bool EN = false, int RV = 0>
+__device__ __forceinline__ void fused_transform(gp<const cpx> __restrict__ tw, int pencil, int kx0, bool ok,
+                                                const DipoleArgs& dip, int t, int h, int pl,
+                                                cpx (&v)[GeoZ<N, RV>::EZ], const double (&sv)[GeoZ<N, RV>::EZ],
+                                                cpx* area, int NX, int NY, gp<double> part) {
     using Gm = GeoZ<N, RV>;
     using FZ = typename Gm::FZ;
-    constexpr int E = Gm::EZ, G = Gm::GZ, A = Gm::AZ;
-    constexpr bool FW = (G <= 64), CW = (2 * G <= 64);
+    constexpr int E = Gm::EZ, G = Gm::GZ;
+    constexpr bool FW = (G <= 64);
     // the odd half's padding twist rides in the transforms (fft, fft_t with h = 1)
     if (h) twist_const<FZ, false>(v);
     fft<FZ, false, FW>(v, t, area, t, area, tw, h);
@@ -751,6 +762,19 @@ __device__ __forceinline__ void fused_body(gp<cpx> __restrict__ X, gp<const cpx>
     if constexpr (EN) fused_energy_store<N, DIM, RV>(acc, ok, pencil, kx0, t, h, pl, NX, NY, part);
     lds_sync<FW>();
     fft_t<FZ, true, FW>(v, t, area, t, area, tw, h);
+}
+
+// fused_transform, the even/odd combination and the store of the pencil if ok.
+template <int N, int DIM, int MODE, int NT = NT_P3, bool EN = false, int RV = 0>
+__device__ __forceinline__ void fused_body(gp<cpx> __restrict__ X, gp<const cpx> __restrict__ tw, int pencil, int kx0,
+                                           bool ok, const DipoleArgs& dip, int t, int h, int pl,
+                                           cpx (&v)[GeoZ<N, RV>::EZ], const double (&sv)[GeoZ<N, RV>::EZ],
+                                           cpx* lds, cpx* area, int NX, int NY, gp<double> part = nullptr) {
+    using Gm = GeoZ<N, RV>;
+    using FZ = typename Gm::FZ;
+    constexpr int E = Gm::EZ, G = Gm::GZ, A = Gm::AZ;
+    constexpr bool FW = (G <= 64), CW = (2 * G <= 64);
+    fused_transform<N, DIM, MODE, EN, RV>(tw, pencil, kx0, ok, dip, t, h, pl, v, sv, area, NX, NY, part);
     gp<cpx> base = X + (size_t)pencil * N;
     if constexpr (FusedRoles<N, RV>::SWAP) {
         // lanes l < 32 (even half) take the odd half's values e < E/2 from lane l + 32,
@@ -928,6 +952,115 @@ __global__ void __launch_bounds__((PZ * 2 * GeoZ<N, RV>::GZ)) k_fused(cpx* __res
             fused_group<N, DIM, MODE, NT, true, PZ, EN, RV>((gp<cpx>)Xg, (gp<const double>)specg, (gp<const cpx>)twg,
                                                             npencils, kx0, dip, g, threadIdx.x, true, lds, Ext(),
                                                             (gp<double>)part);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// P2, P3 and P4 of a small 3D grid in one launch, every kx plane held in LDS: block (kx, hy)
+// transforms the plane's y axis to the ky of parity hy (half of the padded spectrum: the
+// n-point transform of the plane, twisted when hy = 1), runs the fused z pass on those n
+// pencils and transforms them back to y.  The two blocks of a plane leave two halves of the
+// y-inverse's result, H[hy][z][kx][y], which the x-inverse pass adds as it loads.
+//
+// The same transforms on the same plans as the three passes, and the halves are added in their
+// order: the same bits.  What it saves is two launches and the trips of X2 through memory
+// (64 (n+1) n^2 bytes), which at these sizes are latency: every pass is a kernel of 3 to 6 us of
+// which the data's share is below 1 us.
+// Layout of the LDS: row ky (of n) at ky * 2 AZ, the two exchange areas of its z pencil, so a
+// pencil's row is read and written by its own wave only; the y transforms' areas (A slots each,
+// the G <= 8 threads of a transform inside one wave) overlap the rows, block barriers between.
+// ---------------------------------------------------------------------------
+template <int N> struct GeoP {
+    using Gm = Geo<N>;
+    static constexpr int PW = Gm::GZ <= 32 ? 32 / Gm::GZ : 0;                    // z pencils per wave
+    static constexpr int W = PW ? (N + PW - 1) / PW : 99;                        // waves per block
+    static constexpr int T = 64 * W;
+    static constexpr int YW = (N * Gm::G + 63) / 64;                             // waves with y transforms
+    static constexpr int AREAS = YW * 64 / Gm::G;                                // y areas those waves touch
+    static constexpr int ROW = 2 * Gm::AZ;
+    static constexpr int ROWS = W * PW;                                          // z pencils the waves touch
+    static constexpr int LDS = ROWS * ROW > AREAS * Gm::A ? ROWS * ROW : AREAS * Gm::A;
+};
+// Lengths with the plane kernel: the plane's rows fit the LDS of a CU and its waves a block.
+template <int N> constexpr bool plane_fused() {
+    return N <= 64 && Geo<N>::G <= 32 && 64 % Geo<N>::G == 0 && GeoP<N>::T <= 1024 && GeoP<N>::YW <= GeoP<N>::W &&
+           GeoP<N>::LDS * 16 <= 160 * 1024;
+}
+
+template <int N, int MODE, bool EN>
+__global__ void __launch_bounds__((GeoP<N>::T)) k_plane(const cpx* __restrict__ X1g, cpx* __restrict__ H,
+                                                       const double* __restrict__ specg,
+                                                       const cpx* __restrict__ twg, DipoleArgs dip, int zs,
+                                                       double* __restrict__ part) {
+    using Gm = Geo<N>;
+    using P = GeoP<N>;
+    using Fy = typename Gm::F;
+    constexpr int E = Gm::E, G = Gm::G, A = Gm::A, EZ = Gm::EZ, GZ = Gm::GZ, ROW = P::ROW;
+    __shared__ cpx lds[P::LDS];
+    const int tid = threadIdx.x, kx = blockIdx.x >> 1, hy = blockIdx.x & 1;
+    gp<const cpx> tw = (gp<const cpx>)twg;
+    // the z pencil of this thread, its spectrum row loaded ahead
+    int t, h, pl;
+    FusedRoles<N>::get(tid, t, h, pl);
+    const bool ok = pl < N;
+    const int pencil = kx * 2 * N + 2 * (ok ? pl : 0) + hy;
+    double sv[EZ];
+    fused_spec<N, 3, 0>((gp<const double>)specg, pencil, 0, ok, t, h, sv, N);
+
+    // y forward: thread ty of the transform of row z
+    const int ty = tid % G, z = tid / G;
+    const bool yw = __builtin_amdgcn_readfirstlane(tid) < 64 * P::YW, oky = yw && z < N;
+    cpx* const ya = lds + (yw ? z : 0) * A;
+    if (yw) {
+        cpx v[E];
+        gp<const cpx> src = (gp<const cpx>)X1g + ((size_t)(oky ? z : 0) * (N + 1) + kx) * N;
+#pragma unroll
+        for (int e = 0; e < E; ++e) v[e] = oky ? src[ty + G * e] : cmk(0.0, 0.0);
+        if (hy) twist_const<Fy, false>(v);
+        fft<Fy, false, true>(v, ty, ya, ty, ya, tw, hy);
+        lds_barrier();
+        if (oky) {
+#pragma unroll
+            for (int e = 0; e < E; ++e) lds[(ty + G * e) * ROW + z] = v[e];
+        }
+    } else {
+        lds_barrier();
+    }
+    lds_barrier();
+
+    // fused z pass on row pl
+    cpx* const row = lds + pl * ROW;
+    {
+        cpx v[EZ];
+#pragma unroll
+        for (int e = 0; e < EZ; ++e) v[e] = ok ? row[t + GZ * e] : cmk(0.0, 0.0);
+        lds_wave_sync();
+        fused_transform<N, 3, MODE, EN, 0>(tw, pencil, 0, ok, dip, t, h, pl, v, sv, row + h * Gm::AZ, N, N,
+                                           (gp<double>)part);
+        lds_wave_sync();
+#pragma unroll
+        for (int e = 0; e < EZ / 2; ++e) {
+            cpx a = v[e], b = v[e + EZ / 2];
+            swap_halves(a, b);
+            row[t + GZ * (h * (EZ / 2) + e)] = cadd(a, b);
+        }
+    }
+    lds_barrier();
+
+    // y inverse, cropped; only the planes z < zs are needed
+    if (yw) {
+        cpx v[E];
+#pragma unroll
+        for (int e = 0; e < E; ++e) v[e] = oky ? lds[(ty + G * e) * ROW + z] : cmk(0.0, 0.0);
+        lds_barrier();
+        fft_t<Fy, true, true>(v, ty, ya, ty, ya, tw, hy);
+        if (oky && z < zs) {
+            gp<cpx> dst = (gp<cpx>)H + (((size_t)hy * N + z) * (N + 1) + kx) * N;
+#pragma unroll
+            for (int e = 0; e < E; ++e) dst[ty + G * e] = v[e];
+        }
+    } else {
+        lds_barrier();
     }
 }
 
