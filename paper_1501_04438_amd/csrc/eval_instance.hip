@@ -41,6 +41,21 @@ template <int N> constexpr int px_of(int v) {
     // (whole tiles only: a tile that does not divide the grid would pair rows differently)
     return (gs_tile_variants(N) && v == 1 && 2 * P * Geo<N>::A * 16 <= LDS_LIMIT && N % (4 * P) == 0) ? 2 * P : P;
 }
+// Row pairs per block of the x passes of a 2D grid, at most the default: one wave per block
+// (two where a row pair takes more).  A 2D pass has only n / 2 row pairs, so the default tile
+// of 8 pairs leaves most of the chip without a block (n = 192: 12 blocks); the pairs are the
+// same, so are the bits.  One pass alone, default -> this tile, forward / inverse: 128 4.23 ->
+// 3.86 / 3.48 -> 2.86, 192 5.39 -> 4.86 / 4.37 -> 3.40, 256 5.73 -> 5.17 / 4.63 -> 3.64,
+// 384 6.76 -> 5.78 / 5.12 -> 4.26, 512 6.82 -> 5.39 / 5.01 -> 4.04 us; half a wave per block
+// and, beyond 512, runs of one row pair on the transposed side are slower again.
+template <int N> constexpr int px_2d(bool inverse) {
+    constexpr int P = Geo<N>::PPX, G = Geo<N>::G;
+    if (N > 512) return P;
+    const int want = inverse ? 32 : (G < 64 ? 64 : 128);      // the split inverse takes 2 G threads per pair
+    int px = P;
+    while (px > 1 && px % 2 == 0 && px * G > want) px /= 2;
+    return px;
+}
 template <int N> constexpr int py_of(int v) {
     constexpr int P = Geo<N>::PPY;
     if (!gs_tile_variants(N)) return P;
@@ -133,6 +148,7 @@ static hipError_t launch_x_inverse(const EvalArgs& a, hipStream_t s) {
         if ((a.tile_bits >> 10) & 1) return launch_x_inverse_v<Geo<N>::PPX, 1>(a, s);
     }
     if (((a.tile_bits >> 6) & 3) == 1 && px_of<N>(1) != px_of<N>(0)) return launch_x_inverse_v<px_of<N>(1)>(a, s);
+    if (a.d == 2) return launch_x_inverse_v<px_2d<N>(true)>(a, s);
     return launch_x_inverse_v<px_of<N>(0)>(a, s);
 }
 
@@ -156,6 +172,7 @@ static hipError_t launch_x_forward(const EvalArgs& a, hipStream_t s) {
         if ((a.tile_bits >> 9) & 1) return launch_x_forward_v<Geo<N>::PPX, 1>(a, s);
     }
     if ((a.tile_bits & 3) == 1 && px_of<N>(1) != px_of<N>(0)) return launch_x_forward_v<px_of<N>(1)>(a, s);
+    if (a.d == 2) return launch_x_forward_v<px_2d<N>(false)>(a, s);
     return launch_x_forward_v<px_of<N>(0)>(a, s);
 }
 
@@ -310,6 +327,27 @@ int GS_CAT(tile_variants_, GS_N)() {
            (x_radix_variant<N>() ? 64 : 0) | (x_radix_variant<N>() && N <= GS_MAX_N_3D ? 128 : 0);
 }
 
+// The x passes of a grid whose axes have their own n, PX row pairs per block.
+template <int PX>
+static hipError_t launch_x_g(const EvalArgs& a, hipStream_t s, int pass, const Ext& ext) {
+    constexpr int N = GS_N, T = PX * Geo<N>::G;
+    cpx* const X1 = reinterpret_cast<cpx*>(a.X1);
+    const cpx* const tw = reinterpret_cast<const cpx*>(a.twx);
+    const bool hint = (a.hint_bits >> (pass - 1)) & 1;
+    const dim3 gx((ext.ny + 2 * PX - 1) / (2 * PX), ext.nz);
+    if (pass == 1) {
+        if (hint) k_x_r2c_g<N, NT_P1, PX><<<gx, T, 0, s>>>(a.rho, X1, tw, ext);
+        else k_x_r2c_g<N, 0, PX><<<gx, T, 0, s>>>(a.rho, X1, tw, ext);
+    } else if (a.energy && a.oscale != 1.0) {
+        if (hint) k_x_c2r_g<N, NT_P5, true, PX><<<gx, T, 0, s>>>(X1, a.u, tw, ext, a.oscale);
+        else k_x_c2r_g<N, 0, true, PX><<<gx, T, 0, s>>>(X1, a.u, tw, ext, a.oscale);
+    } else {
+        if (hint) k_x_c2r_g<N, NT_P5, false, PX><<<gx, T, 0, s>>>(X1, a.u, tw, ext, 1.0);
+        else k_x_c2r_g<N, 0, false, PX><<<gx, T, 0, s>>>(X1, a.u, tw, ext, 1.0);
+    }
+    return hipGetLastError();
+}
+
 // Pass `pass` of a grid whose axes have their own n, N being the length the pass transforms
 // (x for passes 1 and 5, y for 2 and 4, the fused axis for 3: z in 3D, y in 2D).  One block
 // per tile or pencil group; the cache-hint variants as in the cubic launches.
@@ -324,22 +362,8 @@ hipError_t GS_CAT(launch_eval_g_, GS_N)(const EvalArgs& a, hipStream_t s, int pa
     cpx* const X2 = reinterpret_cast<cpx*>(a.X2);
     const bool hint = (a.hint_bits >> (pass - 1)) & 1;
     if (pass == 1 || pass == 5) {
-        const cpx* const tw = reinterpret_cast<const cpx*>(a.twx);
-        const dim3 gx((ext.ny + 2 * Gm::PPX - 1) / (2 * Gm::PPX), ext.nz);
-        if (pass == 1) {
-            if (hint) k_x_r2c_g<N, NT_P1><<<gx, Gm::TX, 0, s>>>(a.rho, X1, tw, ext);
-            else k_x_r2c_g<N, 0><<<gx, Gm::TX, 0, s>>>(a.rho, X1, tw, ext);
-            return hipGetLastError();
-        }
-        if (a.energy && a.oscale != 1.0) {
-            if (hint) k_x_c2r_g<N, NT_P5, true><<<gx, Gm::TX, 0, s>>>(X1, a.u, tw, ext, a.oscale);
-            else k_x_c2r_g<N, 0, true><<<gx, Gm::TX, 0, s>>>(X1, a.u, tw, ext, a.oscale);
-        } else {
-            if (hint) k_x_c2r_g<N, NT_P5, false><<<gx, Gm::TX, 0, s>>>(X1, a.u, tw, ext, 1.0);
-            else k_x_c2r_g<N, 0, false><<<gx, Gm::TX, 0, s>>>(X1, a.u, tw, ext, 1.0);
-        }
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess || !a.energy) return e;
+        const hipError_t e = a.d == 2 ? launch_x_g<px_2d<N>(false)>(a, s, pass, ext) : launch_x_g<Gm::PPX>(a, s, pass, ext);
+        if (e != hipSuccess || pass == 1 || !a.energy) return e;
         // the energy's pencil sums were written by the fused pass
         return launch_energy_total(a.epart, a.epencils, a.escale, a.energy, s);
     }

@@ -1069,19 +1069,19 @@ __global__ void __launch_bounds__((GeoP<N>::T)) k_plane(const cpx* __restrict__ 
 // transform length N is the n of the axis the pass transforms, the other extents come in
 // `ext`, and every row and pencil is bounds-checked.  One block per tile or pencil group.
 // ---------------------------------------------------------------------------
-template <int N, int NT>
-__global__ void __launch_bounds__(Geo<N>::TX) k_x_r2c_g(const double* __restrict__ rho, cpx* __restrict__ X1,
-                                                        const cpx* __restrict__ tw, Ext ext) {
-    __shared__ cpx lds[Geo<N>::PPX * Geo<N>::A];
-    x_r2c_tile<N, NT, false>((gp<const double>)rho, (gp<cpx>)X1, (gp<const cpx>)tw, blockIdx.x, blockIdx.y,
+template <int N, int NT, int PX = Geo<N>::PPX>
+__global__ void __launch_bounds__((PX * Geo<N>::G)) k_x_r2c_g(const double* __restrict__ rho, cpx* __restrict__ X1,
+                                                              const cpx* __restrict__ tw, Ext ext) {
+    __shared__ cpx lds[PX * Geo<N>::A];
+    x_r2c_tile<N, NT, false, PX>((gp<const double>)rho, (gp<cpx>)X1, (gp<const cpx>)tw, blockIdx.x, blockIdx.y,
                              threadIdx.x, true, lds, ext);
 }
 
-template <int N, int NT, bool SC>
-__global__ void __launch_bounds__(Geo<N>::TX) k_x_c2r_g(const cpx* __restrict__ X1, double* u,
-                                                        const cpx* __restrict__ tw, Ext ext, double oscale) {
-    __shared__ cpx lds[Geo<N>::PPX * Geo<N>::A];
-    x_c2r_tile<N, NT, SC, false>((gp<const cpx>)X1, (gp<double>)u, (gp<const cpx>)tw, blockIdx.x, blockIdx.y,
+template <int N, int NT, bool SC, int PX = Geo<N>::PPX>
+__global__ void __launch_bounds__((PX * Geo<N>::G)) k_x_c2r_g(const cpx* __restrict__ X1, double* u,
+                                                              const cpx* __restrict__ tw, Ext ext, double oscale) {
+    __shared__ cpx lds[PX * Geo<N>::A];
+    x_c2r_tile<N, NT, SC, false, PX>((gp<const cpx>)X1, (gp<double>)u, (gp<const cpx>)tw, blockIdx.x, blockIdx.y,
                                  threadIdx.x, true, lds, ext, oscale);
 }
 
