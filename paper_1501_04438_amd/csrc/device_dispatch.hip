@@ -34,17 +34,18 @@ static hipError_t launch_pass_g(const EvalArgs& a, hipStream_t s, int pass) {
     }
 }
 
-// One block: thread t sums part[t], part[t + 256], ... in order, then the fixed-order block
-// sum; the same bits on every run.  The loads are issued eight at a time (the additions keep
-// their order; a missing term adds 0).
-__global__ void __launch_bounds__(256) k_energy_finish(const double* __restrict__ part, int count, double scale,
-                                                       double* __restrict__ energy) {
-    __shared__ double red[4];
+// One block of T threads: thread t sums part[t], part[t + T], ... in order, then the
+// fixed-order block sum; the same bits on every run.  The loads are issued eight at a time (the
+// additions keep their order; a missing term adds 0).
+template <int T>
+__global__ void __launch_bounds__(T) k_energy_finish(const double* __restrict__ part, int count, double scale,
+                                                     double* __restrict__ energy) {
+    __shared__ double red[T / 64];
     double v = 0.0;
-    for (int i0 = threadIdx.x; i0 < count; i0 += 8 * 256) {
+    for (int i0 = threadIdx.x; i0 < count; i0 += 8 * T) {
         double q[8];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) q[k] = (i0 + 256 * k < count) ? part[i0 + 256 * k] : 0.0;
+        for (int k = 0; k < 8; ++k) q[k] = (i0 + T * k < count) ? part[i0 + T * k] : 0.0;
 #pragma unroll
         for (int k = 0; k < 8; ++k) v += q[k];
     }
@@ -52,11 +53,18 @@ __global__ void __launch_bounds__(256) k_energy_finish(const double* __restrict_
     for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
-    if (threadIdx.x == 0) energy[0] = scale * (((red[0] + red[1]) + red[2]) + red[3]);
+    if (threadIdx.x == 0) {
+        v = red[0];
+#pragma unroll
+        for (int i = 1; i < T / 64; ++i) v += red[i];
+        energy[0] = scale * v;
+    }
 }
 
+// Up to 4096 partials (and the chunk sums of launch_energy_total) 256 threads, else 1024.
 hipError_t launch_energy_finish(const double* part, int count, double scale, double* energy, hipStream_t s) {
-    k_energy_finish<<<1, 256, 0, s>>>(part, count, scale, energy);
+    if (count <= 4096) k_energy_finish<256><<<1, 256, 0, s>>>(part, count, scale, energy);
+    else k_energy_finish<1024><<<1, 1024, 0, s>>>(part, count, scale, energy);
     return hipGetLastError();
 }
 
@@ -86,7 +94,9 @@ constexpr int kEnergyChunks = 256;
 int energy_total_scratch() { return kEnergyChunks; }
 
 hipError_t launch_energy_total(double* part, int count, double scale, double* energy, hipStream_t s) {
-    if (count <= 4096) return launch_energy_finish(part, count, scale, energy, s);
+    // one block reads up to 32768 partials (256 KB) in the time of the second launch it saves
+    // (n = 96: 18.6 k partials, 3.8 + 1.5 us in two launches)
+    if (count <= 32768) return launch_energy_finish(part, count, scale, energy, s);
     const int nb = std::min(kEnergyChunks, (count + 4095) / 4096);
     const int chunk = (count + nb - 1) / nb;
     double* sums = part + count;
