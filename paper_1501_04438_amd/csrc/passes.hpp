@@ -114,6 +114,25 @@ template <int N, int XV = 0> struct GeoX {
     static constexpr int E = F::E, G = F::G;
 };
 
+// Tile of block b of nb, for x passes whose tile covers less than a 128-byte line of the
+// transposed side (PX row pairs: 32 PX bytes, in two runs where the pairs are split): the LPT
+// tiles that share their lines go to blocks 8 apart, so to the same die (blocks are dealt to the
+// 8 dies in turn) at about the same time, and its L2 merges the parts of a line.  Other grids and
+// remainders keep the plain order.
+template <int LPT>
+__device__ __forceinline__ int die_tile(int b, int nb) {
+    if constexpr (LPT <= 1) return b;
+    const int whole = nb / (8 * LPT) * (8 * LPT);
+    if (b >= whole) return b;
+    return (b / (8 * LPT) * 8 + b % 8) * LPT + (b / 8) % LPT;
+}
+// Tiles of PX row pairs that share one line: split pairs p and p + 8 cover 16 PX bytes per run.
+template <int N, int PX> constexpr int line_tiles() {
+    constexpr bool SPLIT = N % (2 * PX) == 0 && Geo<N>::PPX % 8 == 0 && N % (2 * Geo<N>::PPX) == 0;
+    constexpr int run = SPLIT ? 16 * PX : 32 * PX;
+    return run >= 128 ? 1 : 128 / run;
+}
+
 // Extents of a grid whose axes have their own n (x, y, z; 2D: z = 1).  A pass compiled with
 // CUBE = true takes every extent as its transform length N (compile time) and ignores these;
 // with CUBE = false the extents of the axes it does not transform come from here, and every
@@ -235,8 +254,9 @@ __global__ void __launch_bounds__((PX * GeoX<N, XV>::G)) __attribute__((amdgpu_w
 k_x_r2c(const double* __restrict__ rho, cpx* __restrict__ X1,
                                                       const cpx* __restrict__ tw) {
     __shared__ cpx lds[PX * Geo<N>::A];
-    x_r2c_tile<N, NT, true, PX, false, XV>((gp<const double>)rho, (gp<cpx>)X1, (gp<const cpx>)tw, blockIdx.x,
-                                           blockIdx.y, threadIdx.x, true, lds);
+    x_r2c_tile<N, NT, true, PX, false, XV>((gp<const double>)rho, (gp<cpx>)X1, (gp<const cpx>)tw,
+                                           die_tile<line_tiles<N, PX>()>(blockIdx.x, gridDim.x), blockIdx.y,
+                                           threadIdx.x, true, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -418,14 +438,15 @@ __device__ __forceinline__ void x_c2r_tile_split(gp<const cpx> __restrict__ X1, 
 template <int N, int NT = NT_P5, int PX = Geo<N>::PPX, bool SC = false, int XV = 0, bool HV = false>
 __global__ void __launch_bounds__((p5_threads<N, PX, XV>())) k_x_c2r(const cpx* __restrict__ X1, double* __restrict__ u,
                                                                    const cpx* __restrict__ tw, double oscale = 1.0) {
+    const int bx = die_tile<line_tiles<N, PX>()>(blockIdx.x, gridDim.x);
     if constexpr (p5_split<N, PX, XV>()) {
         __shared__ cpx lds[2 * PX * Geo<N>::A];
-        x_c2r_tile_split<N, NT, SC, PX, XV, false, HV>((gp<const cpx>)X1, (gp<double>)u, (gp<const cpx>)tw, blockIdx.x,
-                                            blockIdx.y, threadIdx.x, lds, oscale);
+        x_c2r_tile_split<N, NT, SC, PX, XV, false, HV>((gp<const cpx>)X1, (gp<double>)u, (gp<const cpx>)tw, bx,
+                                                       blockIdx.y, threadIdx.x, lds, oscale);
     } else {
         __shared__ cpx lds[PX * Geo<N>::A];
-        x_c2r_tile<N, NT, SC, true, PX, XV, false, HV>((gp<const cpx>)X1, (gp<double>)u, (gp<const cpx>)tw, blockIdx.x,
-                                            blockIdx.y, threadIdx.x, true, lds, Ext(), oscale);
+        x_c2r_tile<N, NT, SC, true, PX, XV, false, HV>((gp<const cpx>)X1, (gp<double>)u, (gp<const cpx>)tw, bx,
+                                                       blockIdx.y, threadIdx.x, true, lds, Ext(), oscale);
     }
 }
 
