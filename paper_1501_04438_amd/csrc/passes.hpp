@@ -525,8 +525,8 @@ template <int N, int NT = NT_P2, int PY = Geo<N>::PPY, int YV = 0>
 __global__ void __launch_bounds__((PY * GeoX<N, YV>::G)) k_y_fwd(const cpx* __restrict__ X1, cpx* __restrict__ X2,
                                                                 const cpx* __restrict__ tw, int kx0) {
     __shared__ cpx lds[PY * Geo<N>::A];
-    y_fwd_tile<N, NT, true, PY, YV>((gp<const cpx>)X1, (gp<cpx>)X2, (gp<const cpx>)tw, kx0, blockIdx.x, blockIdx.y,
-                                threadIdx.x, true, lds);
+    y_fwd_tile<N, NT, true, PY, YV>((gp<const cpx>)X1, (gp<cpx>)X2, (gp<const cpx>)tw, kx0,
+                                    die_tile<PY == 8 ? 2 : 1>(blockIdx.x, gridDim.x), blockIdx.y, threadIdx.x, true, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -574,8 +574,8 @@ template <int N, int NT = NT_P4, int PY = Geo<N>::PPY, int YV = 0>
 __global__ void __launch_bounds__((PY * GeoX<N, YV>::G)) k_y_inv(const cpx* __restrict__ X2, cpx* __restrict__ X1,
                                                                 const cpx* __restrict__ tw, int kx0) {
     __shared__ cpx lds[PY * Geo<N>::A];
-    y_inv_tile<N, NT, true, PY, YV>((gp<const cpx>)X2, (gp<cpx>)X1, (gp<const cpx>)tw, kx0, blockIdx.x, blockIdx.y,
-                                threadIdx.x, true, lds);
+    y_inv_tile<N, NT, true, PY, YV>((gp<const cpx>)X2, (gp<cpx>)X1, (gp<const cpx>)tw, kx0,
+                                    die_tile<PY == 8 ? 2 : 1>(blockIdx.x, gridDim.x), blockIdx.y, threadIdx.x, true, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -959,6 +959,8 @@ __global__ void __launch_bounds__((PZ * 2 * GeoZ<N, RV>::GZ)) k_fused(cpx* __res
                                                               DipoleArgs dip, double* __restrict__ part = nullptr) {
     __shared__ cpx lds[PZ * 2 * GeoZ<N, RV>::AZ];
     const int ngroups = (fused_slots<N, DIM, RV>(npencils) + PZ - 1) / PZ;
+    // one pencil per block: the +ky and -ky pencils, which read the same spectrum row, on one die
+    constexpr int PAIR = DIM == 3 && PZ == 1 ? 2 : 1;
     if constexpr (!gs_fused_persistent(DIM, N)) {
         // one pencil group per block (the grid must cover all groups).  Without the
         // persistent loop the compiler does not keep the stage twiddles of every thread
@@ -966,8 +968,8 @@ __global__ void __launch_bounds__((PZ * 2 * GeoZ<N, RV>::GZ)) k_fused(cpx* __res
         // registers, two waves per SIMD instead of one
         if ((int)blockIdx.x < ngroups)
             fused_group<N, DIM, MODE, NT, true, PZ, EN, RV>((gp<cpx>)Xg, (gp<const double>)specg, (gp<const cpx>)twg,
-                                                            npencils, kx0, dip, blockIdx.x, threadIdx.x, true, lds,
-                                                            Ext(), (gp<double>)part);
+                                                            npencils, kx0, dip, die_tile<PAIR>(blockIdx.x, ngroups),
+                                                            threadIdx.x, true, lds, Ext(), (gp<double>)part);
     } else {
         for (int g = blockIdx.x; g < ngroups; g += gridDim.x)
             fused_group<N, DIM, MODE, NT, true, PZ, EN, RV>((gp<cpx>)Xg, (gp<const double>)specg, (gp<const cpx>)twg,
@@ -1018,7 +1020,7 @@ __global__ void __launch_bounds__((GeoP<N>::T)) k_plane(const cpx* __restrict__ 
     using Fy = typename Gm::F;
     constexpr int E = Gm::E, G = Gm::G, A = Gm::A, EZ = Gm::EZ, GZ = Gm::GZ, ROW = P::ROW;
     __shared__ cpx lds[P::LDS];
-    const int tid = threadIdx.x, kx = blockIdx.x >> 1, hy = blockIdx.x & 1;
+    const int tid = threadIdx.x, b = die_tile<2>(blockIdx.x, gridDim.x), kx = b >> 1, hy = b & 1;
     gp<const cpx> tw = (gp<const cpx>)twg;
     // the z pencil of this thread, its spectrum row loaded ahead
     int t, h, pl;
@@ -1094,7 +1096,8 @@ template <int N, int NT, int PX = Geo<N>::PPX>
 __global__ void __launch_bounds__((PX * Geo<N>::G)) k_x_r2c_g(const double* __restrict__ rho, cpx* __restrict__ X1,
                                                               const cpx* __restrict__ tw, Ext ext) {
     __shared__ cpx lds[PX * Geo<N>::A];
-    x_r2c_tile<N, NT, false, PX>((gp<const double>)rho, (gp<cpx>)X1, (gp<const cpx>)tw, blockIdx.x, blockIdx.y,
+    x_r2c_tile<N, NT, false, PX>((gp<const double>)rho, (gp<cpx>)X1, (gp<const cpx>)tw,
+                                 die_tile<(PX < 4 ? 4 / PX : 1)>(blockIdx.x, gridDim.x), blockIdx.y,
                              threadIdx.x, true, lds, ext);
 }
 
@@ -1102,7 +1105,8 @@ template <int N, int NT, bool SC, int PX = Geo<N>::PPX>
 __global__ void __launch_bounds__((PX * Geo<N>::G)) k_x_c2r_g(const cpx* __restrict__ X1, double* u,
                                                               const cpx* __restrict__ tw, Ext ext, double oscale) {
     __shared__ cpx lds[PX * Geo<N>::A];
-    x_c2r_tile<N, NT, SC, false, PX>((gp<const cpx>)X1, (gp<double>)u, (gp<const cpx>)tw, blockIdx.x, blockIdx.y,
+    x_c2r_tile<N, NT, SC, false, PX>((gp<const cpx>)X1, (gp<double>)u, (gp<const cpx>)tw,
+                                     die_tile<(PX < 4 ? 4 / PX : 1)>(blockIdx.x, gridDim.x), blockIdx.y,
                                  threadIdx.x, true, lds, ext, oscale);
 }
 
