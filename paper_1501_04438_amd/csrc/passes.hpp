@@ -133,6 +133,15 @@ template <int N, int PX> constexpr int line_tiles() {
     return run >= 128 ? 1 : 128 / run;
 }
 
+// Tiles of one die's run along a row of `tiles` tiles in the 3D x and y passes: from n = 320 a
+// contiguous eighth of the row, so that a die's accesses to X1 and X2 are runs of 1 KB and more
+// instead of every eighth 128-byte line (`part` tiles, the ones that share lines, at least).
+// Measured x passes and y passes together, plain order -> this: 320^3 1652 -> 1616, 384^3 2847 ->
+// 2777, 512^3 6160 -> 5879 us; at 128^3 to 256^3 the same time within 1 %, in 2D (2048^2) 2.5 % slower.
+template <int N> constexpr int die_run(int tiles, int part) {
+    return N >= 320 && tiles / 8 > part ? tiles / 8 : part;
+}
+
 // Extents of a grid whose axes have their own n (x, y, z; 2D: z = 1).  A pass compiled with
 // CUBE = true takes every extent as its transform length N (compile time) and ignores these;
 // with CUBE = false the extents of the axes it does not transform come from here, and every
@@ -246,6 +255,13 @@ __device__ __forceinline__ void x_r2c_tile(gp<const double> __restrict__ rho, gp
     }
 }
 
+// The tile of the calling block of an x pass (3D: one row of tiles per z).
+template <int N, int PX> __device__ __forceinline__ int x_die_tile() {
+    constexpr int part = line_tiles<N, PX>(), run = die_run<N>(N / (2 * PX), part);
+    return run > part && gridDim.y > 1 ? die_tile<run>(blockIdx.x, gridDim.x)
+                                       : die_tile<part>(blockIdx.x, gridDim.x);
+}
+
 // At n = 2048 the compiler's own allocation takes 256 VGPRs + 42 accumulator registers (one wave
 // per SIMD); capped at two waves per SIMD it spills 172 bytes per lane and still runs faster
 // (measured 0.038 -> 0.033 ms for 2D 2048^2; the same cap slows the x-inverse and n = 1024).
@@ -255,8 +271,7 @@ k_x_r2c(const double* __restrict__ rho, cpx* __restrict__ X1,
                                                       const cpx* __restrict__ tw) {
     __shared__ cpx lds[PX * Geo<N>::A];
     x_r2c_tile<N, NT, true, PX, false, XV>((gp<const double>)rho, (gp<cpx>)X1, (gp<const cpx>)tw,
-                                           die_tile<line_tiles<N, PX>()>(blockIdx.x, gridDim.x), blockIdx.y,
-                                           threadIdx.x, true, lds);
+                                           x_die_tile<N, PX>(), blockIdx.y, threadIdx.x, true, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -438,7 +453,7 @@ __device__ __forceinline__ void x_c2r_tile_split(gp<const cpx> __restrict__ X1, 
 template <int N, int NT = NT_P5, int PX = Geo<N>::PPX, bool SC = false, int XV = 0, bool HV = false>
 __global__ void __launch_bounds__((p5_threads<N, PX, XV>())) k_x_c2r(const cpx* __restrict__ X1, double* __restrict__ u,
                                                                    const cpx* __restrict__ tw, double oscale = 1.0) {
-    const int bx = die_tile<line_tiles<N, PX>()>(blockIdx.x, gridDim.x);
+    const int bx = x_die_tile<N, PX>();
     if constexpr (p5_split<N, PX, XV>()) {
         __shared__ cpx lds[2 * PX * Geo<N>::A];
         x_c2r_tile_split<N, NT, SC, PX, XV, false, HV>((gp<const cpx>)X1, (gp<double>)u, (gp<const cpx>)tw, bx,
@@ -526,7 +541,7 @@ __global__ void __launch_bounds__((PY * GeoX<N, YV>::G)) k_y_fwd(const cpx* __re
                                                                 const cpx* __restrict__ tw, int kx0) {
     __shared__ cpx lds[PY * Geo<N>::A];
     y_fwd_tile<N, NT, true, PY, YV>((gp<const cpx>)X1, (gp<cpx>)X2, (gp<const cpx>)tw, kx0,
-                                    die_tile<PY == 8 ? 2 : 1>(blockIdx.x, gridDim.x), blockIdx.y, threadIdx.x, true, lds);
+                                    die_tile<die_run<N>(N / PY, PY == 8 ? 2 : 1)>(blockIdx.x, gridDim.x), blockIdx.y, threadIdx.x, true, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -575,7 +590,7 @@ __global__ void __launch_bounds__((PY * GeoX<N, YV>::G)) k_y_inv(const cpx* __re
                                                                 const cpx* __restrict__ tw, int kx0) {
     __shared__ cpx lds[PY * Geo<N>::A];
     y_inv_tile<N, NT, true, PY, YV>((gp<const cpx>)X2, (gp<cpx>)X1, (gp<const cpx>)tw, kx0,
-                                    die_tile<PY == 8 ? 2 : 1>(blockIdx.x, gridDim.x), blockIdx.y, threadIdx.x, true, lds);
+                                    die_tile<die_run<N>(N / PY, PY == 8 ? 2 : 1)>(blockIdx.x, gridDim.x), blockIdx.y, threadIdx.x, true, lds);
 }
 
 // ---------------------------------------------------------------------------
