@@ -164,7 +164,7 @@ typedef struct {
                                 GS_PLAN_AUTOTUNE picks them by timing            */
     int launch_hints;        /* 1 + the cache-hint bits of the passes (bit p-1 set: pass p
                                 uses its non-temporal hint variant, gs_plan_info.hint_bits);
-                                0 = the compiled default.  Every value gives the same bits;
+                                0 = the default for the grid's size.  Every value gives the same bits;
                                 GS_PLAN_AUTOTUNE picks them by timing            */
 } gs_options;
 
