@@ -67,22 +67,25 @@ __host__ __device__ constexpr int batch_counter(int prob, int pass) { return 1 +
 __device__ __forceinline__ int hw_xcc_id() { return (int)__builtin_amdgcn_s_getreg((3 << 11) | (0 << 6) | 20); }
 
 // Threads and LDS slots of one tile of pass p at size N; tiles per problem.
-// P5 tiles take the single-problem kernel's split form where it has one (the two halves of
-// the padded inverse on the two lane halves of every wave: twice the threads and LDS areas
-// per tile, the same LDS per block, E complex values fewer live per thread).
+// P1 and P5 tiles take the single-problem kernels' split forms (P5 where it has one): the two
+// halves of the padded transform on the two lane halves of every wave, twice the threads and LDS
+// areas per tile, the same LDS per block, fewer values live per thread.
 template <int N> __host__ __device__ constexpr int tile_threads(int pass) {
-    return pass == 1 ? Geo<N>::TX
+    return pass == 1 ? 2 * p1_split_px<N>(3) * Geo<N>::G
                      : (pass == 5 ? p5_threads<N, Geo<N>::PPX>() : (pass == 3 ? Geo<N>::TZ : Geo<N>::TY));
 }
 template <int N> __host__ __device__ constexpr int tile_lds(int pass) {
     return pass == 3   ? 2 * Geo<N>::PPZ * Geo<N>::AZ
-           : pass == 1 ? Geo<N>::PPX * Geo<N>::A
+           : pass == 1 ? 2 * p1_split_px<N>(3) * Geo<N>::A
            : pass == 5 ? (p5_split<N, Geo<N>::PPX>() ? 2 : 1) * Geo<N>::PPX * Geo<N>::A
                        : Geo<N>::PPY * Geo<N>::A;
 }
 template <int N> __host__ __device__ inline int tile_count(int pass, int d) {
     using Gm = Geo<N>;
-    if (pass == 1 || pass == 5) return ((N + 2 * Gm::PPX - 1) / (2 * Gm::PPX)) * (d == 3 ? N : 1);
+    if (pass == 1 || pass == 5) {
+        const int rows = 2 * (pass == 1 ? p1_split_px<N>(3) : Gm::PPX);
+        return ((N + rows - 1) / rows) * (d == 3 ? N : 1);
+    }
     if (pass == 2 || pass == 4) return ((N + Gm::PPY - 1) / Gm::PPY) * (N + 1);
     const int np = (d == 3) ? (N + 1) * 2 * N : N + 1;
     return (np + Gm::PPZ - 1) / Gm::PPZ;
@@ -130,9 +133,9 @@ __device__ __forceinline__ void batch_tile(const BatchProblem& P, int tile0, int
     const gp<const double> spec = (gp<const double>)P.spec;
     const gp<const cpx> tw = (gp<const cpx>)P.tw;
     if constexpr (PASS == 1 || PASS == 5) {
-        constexpr int nbx = (N + 2 * Gm::PPX - 1) / (2 * Gm::PPX);
+        constexpr int PX = PASS == 1 ? p1_split_px<N>(3) : Gm::PPX, nbx = (N + 2 * PX - 1) / (2 * PX);
         const int bx = tile % nbx, z = tile / nbx;
-        if constexpr (PASS == 1) x_r2c_tile<N, NT_P1, true, Gm::PPX, true>(rho, X1, tw, bx, z, tid, active, l);
+        if constexpr (PASS == 1) x_r2c_tile_split<N, NT_P1, PX>(rho, X1, tw, bx, z, tid, l, active);
         else if constexpr (p5_split<N, Gm::PPX>())
             x_c2r_tile_split<N, NT_P5, false, Gm::PPX>(X1, u, tw, bx, z, tid, l, 1.0, active);
         else x_c2r_tile<N>(X1, u, tw, bx, z, tid, active, l);
@@ -189,8 +192,7 @@ __device__ __forceinline__ void batch_task(const BatchProblem& P, const BatchTas
 // The union kernels (every size's tile code in one function) are held to three waves per
 // SIMD, which their LDS (three blocks per CU) allows: 168 VGPRs with a few dozen bytes of
 // spill in the 96-point dipolar fused code, against 225 VGPRs (two waves) unbounded; the tile
-// codes keep fewer values live for this (P1 loads its rows again for the second half, P5
-// runs the split form).  Measured on the 64-problem workload: queue 2.66 -> 2.52 ms, phased
+// codes keep fewer values live for this (P1 and P5 run their split forms).  Measured on the 64-problem workload: queue 2.66 -> 2.52 ms, phased
 // 2.52 -> 2.41 ms, the same bits.
 constexpr int BATCH_UNION_WAVES = 3;
 

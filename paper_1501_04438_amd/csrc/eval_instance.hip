@@ -94,6 +94,53 @@ static hipError_t launch_x_inverse_v(const EvalArgs& a, hipStream_t s) {
     return launch_energy_total(a.epart, a.epencils, a.escale, a.energy, s);
 }
 
+template <int PX, int XV = 0>
+static hipError_t launch_x_forward_v(const EvalArgs& a, hipStream_t s) {
+    constexpr int N = GS_N;
+    constexpr int T = PX * GeoX<N, XV>::G;
+    const cpx* const tw = reinterpret_cast<const cpx*>(a.tw);
+    cpx* const X1 = reinterpret_cast<cpx*>(a.X1);
+    const dim3 gx((N + 2 * PX - 1) / (2 * PX), a.d == 3 ? N : 1);
+    if ((a.hint_bits >> 0) & 1) k_x_r2c<N, NT_P1, PX, XV><<<gx, T, 0, s>>>(a.rho, X1, tw);
+    else k_x_r2c<N, 0, PX, XV><<<gx, T, 0, s>>>(a.rho, X1, tw);
+    return hipGetLastError();
+}
+
+// P1 with its halves on the lane halves (x_r2c_tile_split), PX row pairs per block; with the
+// density at its own extents where a.emb.  PX = 0: the pass keeps x_r2c_tile.
+template <int PX>
+static hipError_t launch_x_forward_split(const EvalArgs& a, hipStream_t s) {
+    constexpr int N = GS_N;
+    const cpx* const tw = reinterpret_cast<const cpx*>(a.tw);
+    cpx* const X1 = reinterpret_cast<cpx*>(a.X1);
+    const bool hint = a.hint_bits & 1;
+    Ext ext;
+    ext.nx = a.px;
+    ext.ny = a.py;
+    ext.nz = a.d == 3 ? a.pz : 1;
+    if constexpr (PX > 0) {
+        constexpr int T = 2 * PX * Geo<N>::G;
+        const dim3 gx((N + 2 * PX - 1) / (2 * PX), a.d == 3 ? N : 1);
+        if (a.emb) {
+            if (hint) k_x_r2c_emb_split<N, NT_P1, PX><<<gx, T, 0, s>>>(a.rho, X1, tw, ext);
+            else k_x_r2c_emb_split<N, 0, PX><<<gx, T, 0, s>>>(a.rho, X1, tw, ext);
+        } else {
+            if (hint) k_x_r2c_split<N, NT_P1, PX><<<gx, T, 0, s>>>(a.rho, X1, tw);
+            else k_x_r2c_split<N, 0, PX><<<gx, T, 0, s>>>(a.rho, X1, tw);
+        }
+    } else {
+        constexpr int P = Geo<N>::PPX, T = Geo<N>::TX;
+        const dim3 gx((N + 2 * P - 1) / (2 * P), a.d == 3 ? N : 1);
+        if (a.emb) {
+            if (hint) k_x_r2c_emb<N, NT_P1><<<gx, T, 0, s>>>(a.rho, X1, tw, ext);
+            else k_x_r2c_emb<N, 0><<<gx, T, 0, s>>>(a.rho, X1, tw, ext);
+        } else {
+            return launch_x_forward_v<P>(a, s);
+        }
+    }
+    return hipGetLastError();
+}
+
 // Padding to B_3 on a cubic transform grid (lengths 3n/2): P1 and P5 with the density and the
 // potential at their own extents (a.px, a.py, a.pz), at the default tile.
 template <bool HV = false>
@@ -109,10 +156,7 @@ static hipError_t launch_x_emb(const EvalArgs& a, hipStream_t s, int pass) {
         const cpx* const tw = reinterpret_cast<const cpx*>(a.tw);
         dim3 gx((N + 2 * Gm::PPX - 1) / (2 * Gm::PPX), a.d == 3 ? N : 1);
         if (pass == 1) {
-            cpx* const X1 = reinterpret_cast<cpx*>(a.X1);
-            if (a.hint_bits & 1) k_x_r2c_emb<N, NT_P1><<<gx, Gm::TX, 0, s>>>(a.rho, X1, tw, ext);
-            else k_x_r2c_emb<N, 0><<<gx, Gm::TX, 0, s>>>(a.rho, X1, tw, ext);
-            return hipGetLastError();
+            return launch_x_forward_split<p1_split_px<N>(3)>(a, s);
         }
         const cpx* const X1 = reinterpret_cast<const cpx*>(HV ? a.X2 : a.X1);
         constexpr int T = p5_threads<N, Gm::PPX>();
@@ -152,18 +196,6 @@ static hipError_t launch_x_inverse(const EvalArgs& a, hipStream_t s) {
     return launch_x_inverse_v<px_of<N>(0)>(a, s);
 }
 
-template <int PX, int XV = 0>
-static hipError_t launch_x_forward_v(const EvalArgs& a, hipStream_t s) {
-    constexpr int N = GS_N;
-    constexpr int T = PX * GeoX<N, XV>::G;
-    const cpx* const tw = reinterpret_cast<const cpx*>(a.tw);
-    cpx* const X1 = reinterpret_cast<cpx*>(a.X1);
-    const dim3 gx((N + 2 * PX - 1) / (2 * PX), a.d == 3 ? N : 1);
-    if ((a.hint_bits >> 0) & 1) k_x_r2c<N, NT_P1, PX, XV><<<gx, T, 0, s>>>(a.rho, X1, tw);
-    else k_x_r2c<N, 0, PX, XV><<<gx, T, 0, s>>>(a.rho, X1, tw);
-    return hipGetLastError();
-}
-
 // Tile bit 9: the x-forward pass's radix-plan variant, as bit 10 for the x-inverse pass.
 static hipError_t launch_x_forward(const EvalArgs& a, hipStream_t s) {
     constexpr int N = GS_N;
@@ -172,8 +204,7 @@ static hipError_t launch_x_forward(const EvalArgs& a, hipStream_t s) {
         if ((a.tile_bits >> 9) & 1) return launch_x_forward_v<Geo<N>::PPX, 1>(a, s);
     }
     if ((a.tile_bits & 3) == 1 && px_of<N>(1) != px_of<N>(0)) return launch_x_forward_v<px_of<N>(1)>(a, s);
-    if (a.d == 2) return launch_x_forward_v<px_2d<N>(false)>(a, s);
-    return launch_x_forward_v<px_of<N>(0)>(a, s);
+    return a.d == 2 ? launch_x_forward_split<p1_split_px<N>(2)>(a, s) : launch_x_forward_split<p1_split_px<N>(3)>(a, s);
 }
 
 // y passes (3D) with PY z-pencils per block: 2 forward, 4 inverse.

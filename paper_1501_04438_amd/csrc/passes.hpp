@@ -157,14 +157,10 @@ struct Ext {
 // ---------------------------------------------------------------------------
 // PX: row pairs per block (a tile-shape variant; the pairing of rows is the same for every PX,
 // so every variant computes the same bits)
-// RL: the rows are loaded again for the second half instead of being kept in registers across
-// both (same values, same bits; E fewer complex values live through the first half's transform,
-// which the batched kernels, sized for every length at once, need for their occupancy)
 // XV: radix plan of the row transforms (XPlan).
 // EMB (with CUBE): the density is the first ext.nx x ext.ny x ext.nz points of the transform
 // grid, read from an array of those extents, zeros elsewhere (padding to B_3 without a copy).
-template <int N, int NT = NT_P1, bool CUBE = true, int PX = Geo<N>::PPX, bool RL = false, int XV = 0,
-          bool EMB = false>
+template <int N, int NT = NT_P1, bool CUBE = true, int PX = Geo<N>::PPX, int XV = 0, bool EMB = false>
 __device__ __forceinline__ void x_r2c_tile(gp<const double> __restrict__ rho, gp<cpx> __restrict__ X1,
                                            gp<const cpx> __restrict__ tw, int bx, int z, int tid, bool active,
                                            cpx* lds, Ext ext = Ext()) {
@@ -188,9 +184,9 @@ __device__ __forceinline__ void x_r2c_tile(gp<const double> __restrict__ rho, gp
     const int qA = bx * PP + pA, rowA = SPLIT ? 16 * (qA / 8) + qA % 8 : 2 * qA;
     const int qB = bx * PP + pB, rowB = SPLIT ? 16 * (qB / 8) + qB % 8 : 2 * qB;
 
-    cpx x[RL ? 1 : E];
+    cpx x[E];
     if constexpr (EMB) {
-        static_assert(CUBE && !RL, "embedded density on the cubic tiles");
+        static_assert(CUBE, "embedded density on the cubic tiles");
         const bool r0 = okA && z < ext.nz && rowA < ext.ny, r1 = okA && z < ext.nz && rowA + RS < ext.ny;
         gp<const double> ra = rho + ((size_t)z * ext.ny + rowA) * ext.nx;
 #pragma unroll
@@ -199,7 +195,7 @@ __device__ __forceinline__ void x_r2c_tile(gp<const double> __restrict__ rho, gp
             const bool in = j < ext.nx;
             x[e] = cmk(r0 && in ? ldg<NT & 1>(ra + j) : 0.0, r1 && in ? ldg<NT & 1>(ra + (size_t)RS * ext.nx + j) : 0.0);
         }
-    } else if constexpr (!RL) {
+    } else {
         gp<const double> ra = rho + ((size_t)z * NY + rowA) * N;
 #pragma unroll
         for (int e = 0; e < E; ++e) {
@@ -211,20 +207,8 @@ __device__ __forceinline__ void x_r2c_tile(gp<const double> __restrict__ rho, gp
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
         cpx v[E];
-        if constexpr (RL) {
-            const double* rb = (const double*)rho;
-            // an opaque base for the second load, so that it is not merged with the first
-            if (h) asm volatile("" : "+s"(rb));
-            gp<const double> ra = (gp<const double>)rb + ((size_t)z * NY + rowA) * N;
 #pragma unroll
-            for (int e = 0; e < E; ++e) {
-                const int j = tA + G * e;
-                v[e] = okA ? cmk(ldg<NT & 1>(ra + j), ldg<NT & 1>(ra + (size_t)RS * N + j)) : cmk(0.0, 0.0);
-            }
-        } else {
-#pragma unroll
-            for (int e = 0; e < E; ++e) v[e] = x[e];
-        }
+        for (int e = 0; e < E; ++e) v[e] = x[e];
         // the separate twist measured faster here than the twisted roots (its h = 1 roots
         // of the 16 x 16 plan double the stage-2 power products in the unrolled h loop)
         if (h) twist_in<Fx>(v, tA, tw);
@@ -270,8 +254,89 @@ __global__ void __launch_bounds__((PX * GeoX<N, XV>::G)) __attribute__((amdgpu_w
 k_x_r2c(const double* __restrict__ rho, cpx* __restrict__ X1,
                                                       const cpx* __restrict__ tw) {
     __shared__ cpx lds[PX * Geo<N>::A];
-    x_r2c_tile<N, NT, true, PX, false, XV>((gp<const double>)rho, (gp<cpx>)X1, (gp<const cpx>)tw,
+    x_r2c_tile<N, NT, true, PX, XV>((gp<const double>)rho, (gp<cpx>)X1, (gp<const cpx>)tw,
                                            x_die_tile<N, PX>(), blockIdx.y, threadIdx.x, true, lds);
+}
+
+// Row pairs per block of x_r2c_tile_split, 0 where the pass keeps x_r2c_tile.  3D up to n = 224
+// (the pass is a few rounds of blocks at most, bound by the length of a thread's chain: one half
+// instead of two, half the registers), the default tile or the pairs that fill half a wave; 2D at
+// every length but 1536, one wave per block up to n = 512 (px_2d).  Measured alone, x_r2c_tile ->
+// split: 3D 48 4.56 -> 3.43, 64 4.07 -> 3.61, 96 7.83 -> 7.30, 112 16.9 -> 12.2, 128 11.9 -> 10.6,
+// 160 28.1 -> 22.1, 192 34.3 -> 28.9, 224 66.5 -> 65.1, but 256 66.6 -> 79.2, 512 576 -> 712 us;
+// 2D 192 4.87 -> 3.82, 512 5.37 -> 4.87, 1024 11.1 -> 10.4, 2048 31.8 -> 29.4, 1536 21.5 -> 23.1 us.
+template <int N> constexpr int p1_split_px(int d) {
+    constexpr int P = Geo<N>::PPX, G = Geo<N>::G, H = G >= 32 ? 1 : 32 / G;
+    if (d == 3) return N > 224 ? 0 : (P > H ? P : H);
+    return N == 1536 ? 0 : (N <= 512 ? H : P);
+}
+
+// P1 of a cubic grid with the two halves of the padded transform (h = 0, 1) on the two 32-lane
+// halves of every wave, as x_c2r_tile_split: twice the threads and LDS areas per row pair, each
+// thread transforming, splitting and storing one half instead of both in turn.  The same
+// arithmetic per half as x_r2c_tile, so the same bits.  EMB as there.
+template <int N, int NT, int PX, bool EMB = false>
+__device__ __forceinline__ void x_r2c_tile_split(gp<const double> __restrict__ rho, gp<cpx> __restrict__ X1,
+                                                 gp<const cpx> __restrict__ tw, int bx, int z, int tid, cpx* lds,
+                                                 bool active = true, Ext ext = Ext()) {
+    using Gm = Geo<N>;
+    using Fx = typename Gm::F;
+    constexpr int E = Fx::E, G = Fx::G, PP = PX, A = Gm::A;
+    static_assert((PX * G) % 32 == 0, "whole half-waves");
+    const int w = tid >> 6, l = tid & 63, h = l >> 5;
+    const int tq = 32 * w + (l & 31);           // thread within its half
+    const int tA = tq % G, pA = tq / G;         // load role: consecutive x
+    const int pB = tq % PP, tB = tq / PP;       // store role: consecutive y
+    constexpr bool FULL = (N % (2 * PP) == 0);
+    constexpr bool SPLIT = FULL && Gm::PPX % 8 == 0 && N % (2 * Gm::PPX) == 0;
+    constexpr int RS = SPLIT ? 8 : 1;
+    const int qA = bx * PP + pA, rowA = SPLIT ? 16 * (qA / 8) + qA % 8 : 2 * qA;
+    const int qB = bx * PP + pB, rowB = SPLIT ? 16 * (qB / 8) + qB % 8 : 2 * qB;
+    const bool okA = active && (FULL || 2 * qA < N), okB = active && (FULL || 2 * qB < N);
+    cpx v[E];
+    const int OX = EMB ? ext.nx : N, OY = EMB ? ext.ny : N;
+    const bool r0 = okA && (!EMB || (z < ext.nz && rowA < ext.ny));
+    const bool r1 = okA && (!EMB || (z < ext.nz && rowA + RS < ext.ny));
+    gp<const double> ra = rho + ((size_t)z * OY + rowA) * OX;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int j = tA + G * e;
+        const bool in = !EMB || j < ext.nx;
+        v[e] = cmk(r0 && in ? ldg<NT & 1>(ra + j) : 0.0, r1 && in ? ldg<NT & 1>(ra + (size_t)RS * OX + j) : 0.0);
+    }
+    if (h) twist_in<Fx>(v, tA, tw);
+    cpx* const aA = lds + (h * PP + pA) * A;
+    cpx* const aB = lds + (h * PP + pB) * A;
+    fft<Fx, false>(v, tA, aA, tB, aB, tw);
+    lds_barrier();
+#pragma unroll
+    for (int e = 0; e < E; ++e) aB[lds_pad(tB + G * e)] = v[e];
+    lds_barrier();
+    gp<cpx> out = X1 + (size_t)z * (N + 1) * N + rowB;
+#pragma unroll
+    for (int e = 0; e <= E / 2; ++e) {
+        if (e == E / 2 && !(h == 0 && tB == 0)) continue;
+        const int k = tB + G * e;
+        if (okB) {
+            const int kp = h ? (N - 1 - k) : ((N - k) % N);
+            const cpx zk = v[e], zp = aB[lds_pad(kp)];
+            const cpx sa = cmk(0.5 * (zk.x + zp.x), 0.5 * (zk.y - zp.y));       // (Z + conj P)/2
+            const cpx df = cmk(zk.x - zp.x, zk.y + zp.y);                        //  Z - conj P
+            const cpx sb = cmk(0.5 * df.y, -0.5 * df.x);                         // /(2i)
+            gp<cpx> o = out + (size_t)(2 * k + h) * N;
+            stg<(NT & 2) != 0>(o, sa);
+            stg<(NT & 2) != 0>(o + RS, sb);
+        }
+    }
+}
+
+template <int N, int NT, int PX>
+__global__ void __launch_bounds__((2 * PX * Geo<N>::G)) k_x_r2c_split(const double* __restrict__ rho,
+                                                                     cpx* __restrict__ X1,
+                                                                     const cpx* __restrict__ tw) {
+    __shared__ cpx lds[2 * PX * Geo<N>::A];
+    x_r2c_tile_split<N, NT, PX>((gp<const double>)rho, (gp<cpx>)X1, (gp<const cpx>)tw, x_die_tile<N, PX>(),
+                                blockIdx.y, threadIdx.x, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -465,6 +530,15 @@ __global__ void __launch_bounds__((p5_threads<N, PX, XV>())) k_x_c2r(const cpx* 
     }
 }
 
+template <int N, int NT, int PX>
+__global__ void __launch_bounds__((2 * PX * Geo<N>::G)) k_x_r2c_emb_split(const double* __restrict__ rho,
+                                                                         cpx* __restrict__ X1,
+                                                                         const cpx* __restrict__ tw, Ext ext) {
+    __shared__ cpx lds[2 * PX * Geo<N>::A];
+    x_r2c_tile_split<N, NT, PX, true>((gp<const double>)rho, (gp<cpx>)X1, (gp<const cpx>)tw, x_die_tile<N, PX>(),
+                                      blockIdx.y, threadIdx.x, lds, true, ext);
+}
+
 // P1 and P5 of padding to B_3 on a cubic transform grid: the density (ext points per axis, in
 // the first points of each axis) read, and the potential written, in place of copies into and
 // out of a grid-sized array.
@@ -472,8 +546,8 @@ template <int N, int NT>
 __global__ void __launch_bounds__(Geo<N>::TX) __attribute__((amdgpu_waves_per_eu(N == 2048 ? 2 : 1)))
 k_x_r2c_emb(const double* __restrict__ rho, cpx* __restrict__ X1, const cpx* __restrict__ tw, Ext ext) {
     __shared__ cpx lds[Geo<N>::PPX * Geo<N>::A];
-    x_r2c_tile<N, NT, true, Geo<N>::PPX, false, 0, true>((gp<const double>)rho, (gp<cpx>)X1, (gp<const cpx>)tw,
-                                                         blockIdx.x, blockIdx.y, threadIdx.x, true, lds, ext);
+    x_r2c_tile<N, NT, true, Geo<N>::PPX, 0, true>((gp<const double>)rho, (gp<cpx>)X1, (gp<const cpx>)tw,
+                                                  blockIdx.x, blockIdx.y, threadIdx.x, true, lds, ext);
 }
 
 template <int N, int NT, bool SC, bool HV = false>
