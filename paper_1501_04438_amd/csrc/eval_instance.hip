@@ -41,19 +41,17 @@ template <int N> constexpr int px_of(int v) {
     // (whole tiles only: a tile that does not divide the grid would pair rows differently)
     return (gs_tile_variants(N) && v == 1 && 2 * P * Geo<N>::A * 16 <= LDS_LIMIT && N % (4 * P) == 0) ? 2 * P : P;
 }
-// Row pairs per block of the x passes of a 2D grid, at most the default: one wave per block
+// Row pairs per block of the x-inverse pass of a 2D grid, at most the default: one wave per block
 // (two where a row pair takes more).  A 2D pass has only n / 2 row pairs, so the default tile
 // of 8 pairs leaves most of the chip without a block (n = 192: 12 blocks); the pairs are the
-// same, so are the bits.  One pass alone, default -> this tile, forward / inverse: 128 4.23 ->
-// 3.86 / 3.48 -> 2.86, 192 5.39 -> 4.86 / 4.37 -> 3.40, 256 5.73 -> 5.17 / 4.63 -> 3.64,
-// 384 6.76 -> 5.78 / 5.12 -> 4.26, 512 6.82 -> 5.39 / 5.01 -> 4.04 us; half a wave per block
-// and, beyond 512, runs of one row pair on the transposed side are slower again.
-template <int N> constexpr int px_2d(bool inverse) {
+// same, so are the bits.  The pass alone, default -> this tile: 128 3.48 -> 2.86, 192 4.37 ->
+// 3.40, 256 4.63 -> 3.64, 384 5.12 -> 4.26, 512 5.01 -> 4.04 us; beyond 512, runs of one row pair
+// on the transposed side are slower again.
+template <int N> constexpr int px_2d() {
     constexpr int P = Geo<N>::PPX, G = Geo<N>::G;
     if (N > 512) return P;
-    const int want = inverse ? 32 : (G < 64 ? 64 : 128);      // the split inverse takes 2 G threads per pair
     int px = P;
-    while (px > 1 && px % 2 == 0 && px * G > want) px /= 2;
+    while (px > 1 && px % 2 == 0 && px * G > 32) px /= 2;      // the split inverse takes 2 G threads per pair
     return px;
 }
 template <int N> constexpr int py_of(int v) {
@@ -192,7 +190,7 @@ static hipError_t launch_x_inverse(const EvalArgs& a, hipStream_t s) {
         if ((a.tile_bits >> 10) & 1) return launch_x_inverse_v<Geo<N>::PPX, 1>(a, s);
     }
     if (((a.tile_bits >> 6) & 3) == 1 && px_of<N>(1) != px_of<N>(0)) return launch_x_inverse_v<px_of<N>(1)>(a, s);
-    if (a.d == 2) return launch_x_inverse_v<px_2d<N>(true)>(a, s);
+    if (a.d == 2) return launch_x_inverse_v<px_2d<N>()>(a, s);
     return launch_x_inverse_v<px_of<N>(0)>(a, s);
 }
 
@@ -237,6 +235,18 @@ static hipError_t launch_y(const EvalArgs& a, hipStream_t s, int pass) {
     static_assert(N <= GS_MAX_N_3D, "the y passes run in 3D only");
     if constexpr (x_radix_variant<N>()) {
         if ((a.tile_bits >> (pass == 2 ? 11 : 12)) & 1) return launch_y_v<Geo<N>::PPY, 1>(a, s, pass);
+    }
+    if constexpr (p4_split<N>()) {
+        if (pass == 4) {
+            constexpr int PY = 8, T = 2 * PY * Geo<N>::G;
+            const dim3 gy(((a.emb ? a.pz : N) + PY - 1) / PY, a.kxn);
+            const cpx* const X2 = reinterpret_cast<const cpx*>(a.X2);
+            cpx* const X1 = reinterpret_cast<cpx*>(a.X1);
+            const cpx* const tw = reinterpret_cast<const cpx*>(a.tw);
+            if ((a.hint_bits >> 3) & 1) k_y_inv_split<N, NT_P4, PY><<<gy, T, 0, s>>>(X2, X1, tw, a.kx0);
+            else k_y_inv_split<N, 0, PY><<<gy, T, 0, s>>>(X2, X1, tw, a.kx0);
+            return hipGetLastError();
+        }
     }
     const int v = (a.tile_bits >> 2) & 3;
     if (v == 1 && py_of<N>(1) != py_of<N>(0)) return launch_y_v<py_of<N>(1)>(a, s, pass);
@@ -358,23 +368,108 @@ int GS_CAT(tile_variants_, GS_N)() {
            (x_radix_variant<N>() ? 64 : 0) | (x_radix_variant<N>() && N <= GS_MAX_N_3D ? 128 : 0);
 }
 
-// The x passes of a grid whose axes have their own n, PX row pairs per block.
-template <int PX>
+// The x passes of a grid whose axes have their own n: where the rows fill the tiles (a multiple of
+// twice the default tile's pairs, so that they pair as on a cubic grid) the cubic passes' forms,
+// PF (forward, 0: not split) and PI (inverse) row pairs per block; otherwise the bounds-checked
+// tile of PX pairs.  128 x 256 x 512: forward 92.9 -> 71, inverse 101.5 -> 82 us.
+template <int PX, int PF, int PI>
 static hipError_t launch_x_g(const EvalArgs& a, hipStream_t s, int pass, const Ext& ext) {
-    constexpr int N = GS_N, T = PX * Geo<N>::G;
+    constexpr int N = GS_N, G = Geo<N>::G, P0 = Geo<N>::PPX;
     cpx* const X1 = reinterpret_cast<cpx*>(a.X1);
     const cpx* const tw = reinterpret_cast<const cpx*>(a.twx);
     const bool hint = (a.hint_bits >> (pass - 1)) & 1;
-    const dim3 gx((ext.ny + 2 * PX - 1) / (2 * PX), ext.nz);
+    const bool sc = a.energy && a.oscale != 1.0;
+    auto grid = [&](int px) { return dim3((ext.ny + 2 * px - 1) / (2 * px), ext.nz); };
+    if (ext.ny % (2 * P0) == 0 && (pass == 5 || PF == 0 || ext.ny % (2 * (PF > P0 ? PF : P0)) == 0)) {
+        if (pass == 1) {
+            if constexpr (PF > 0) {
+                if (hint) k_x_r2c_g_split<N, NT_P1, PF><<<grid(PF), 2 * PF * G, 0, s>>>(a.rho, X1, tw, ext);
+                else k_x_r2c_g_split<N, 0, PF><<<grid(PF), 2 * PF * G, 0, s>>>(a.rho, X1, tw, ext);
+            } else {
+                if (hint) k_x_r2c_g<N, NT_P1, P0, true><<<grid(P0), P0 * G, 0, s>>>(a.rho, X1, tw, ext);
+                else k_x_r2c_g<N, 0, P0, true><<<grid(P0), P0 * G, 0, s>>>(a.rho, X1, tw, ext);
+            }
+        } else if constexpr (p5_split<N, PI>()) {
+            constexpr int T = 2 * PI * G;
+            if (sc) {
+                if (hint) k_x_c2r_g_split<N, NT_P5, true, PI><<<grid(PI), T, 0, s>>>(X1, a.u, tw, ext, a.oscale);
+                else k_x_c2r_g_split<N, 0, true, PI><<<grid(PI), T, 0, s>>>(X1, a.u, tw, ext, a.oscale);
+            } else {
+                if (hint) k_x_c2r_g_split<N, NT_P5, false, PI><<<grid(PI), T, 0, s>>>(X1, a.u, tw, ext, 1.0);
+                else k_x_c2r_g_split<N, 0, false, PI><<<grid(PI), T, 0, s>>>(X1, a.u, tw, ext, 1.0);
+            }
+        } else {
+            if (sc) {
+                if (hint) k_x_c2r_g<N, NT_P5, true, P0, true><<<grid(P0), P0 * G, 0, s>>>(X1, a.u, tw, ext, a.oscale);
+                else k_x_c2r_g<N, 0, true, P0, true><<<grid(P0), P0 * G, 0, s>>>(X1, a.u, tw, ext, a.oscale);
+            } else {
+                if (hint) k_x_c2r_g<N, NT_P5, false, P0, true><<<grid(P0), P0 * G, 0, s>>>(X1, a.u, tw, ext, 1.0);
+                else k_x_c2r_g<N, 0, false, P0, true><<<grid(P0), P0 * G, 0, s>>>(X1, a.u, tw, ext, 1.0);
+            }
+        }
+        return hipGetLastError();
+    }
+    constexpr int T = PX * G;
     if (pass == 1) {
-        if (hint) k_x_r2c_g<N, NT_P1, PX><<<gx, T, 0, s>>>(a.rho, X1, tw, ext);
-        else k_x_r2c_g<N, 0, PX><<<gx, T, 0, s>>>(a.rho, X1, tw, ext);
-    } else if (a.energy && a.oscale != 1.0) {
-        if (hint) k_x_c2r_g<N, NT_P5, true, PX><<<gx, T, 0, s>>>(X1, a.u, tw, ext, a.oscale);
-        else k_x_c2r_g<N, 0, true, PX><<<gx, T, 0, s>>>(X1, a.u, tw, ext, a.oscale);
+        if (hint) k_x_r2c_g<N, NT_P1, PX><<<grid(PX), T, 0, s>>>(a.rho, X1, tw, ext);
+        else k_x_r2c_g<N, 0, PX><<<grid(PX), T, 0, s>>>(a.rho, X1, tw, ext);
+    } else if (sc) {
+        if (hint) k_x_c2r_g<N, NT_P5, true, PX><<<grid(PX), T, 0, s>>>(X1, a.u, tw, ext, a.oscale);
+        else k_x_c2r_g<N, 0, true, PX><<<grid(PX), T, 0, s>>>(X1, a.u, tw, ext, a.oscale);
     } else {
-        if (hint) k_x_c2r_g<N, NT_P5, false, PX><<<gx, T, 0, s>>>(X1, a.u, tw, ext, 1.0);
-        else k_x_c2r_g<N, 0, false, PX><<<gx, T, 0, s>>>(X1, a.u, tw, ext, 1.0);
+        if (hint) k_x_c2r_g<N, NT_P5, false, PX><<<grid(PX), T, 0, s>>>(X1, a.u, tw, ext, 1.0);
+        else k_x_c2r_g<N, 0, false, PX><<<grid(PX), T, 0, s>>>(X1, a.u, tw, ext, 1.0);
+    }
+    return hipGetLastError();
+}
+
+// The y passes (3D) and the fused pass of such a grid; FT: the extents fill the tiles.
+template <int N, bool FT>
+static hipError_t launch_y_g(const EvalArgs& a, hipStream_t s, int pass, const Ext& ext) {
+    static_assert(N <= GS_MAX_N_3D, "the y passes run in 3D only");
+    cpx* const X1 = reinterpret_cast<cpx*>(a.X1);
+    cpx* const X2 = reinterpret_cast<cpx*>(a.X2);
+    const cpx* const tw = reinterpret_cast<const cpx*>(a.twy);
+    const bool hint = (a.hint_bits >> (pass - 1)) & 1;
+    const dim3 gy((ext.nz + Geo<N>::PPY - 1) / Geo<N>::PPY, a.kxn);
+    constexpr int T = Geo<N>::TY;
+    if (pass == 2) {
+        if (hint) k_y_fwd_g<N, NT_P2, FT><<<gy, T, 0, s>>>(X1, X2, tw, a.kx0, ext);
+        else k_y_fwd_g<N, 0, FT><<<gy, T, 0, s>>>(X1, X2, tw, a.kx0, ext);
+    } else {
+        if (hint) k_y_inv_g<N, NT_P4, FT><<<gy, T, 0, s>>>(X2, X1, tw, a.kx0, ext);
+        else k_y_inv_g<N, 0, FT><<<gy, T, 0, s>>>(X2, X1, tw, a.kx0, ext);
+    }
+    return hipGetLastError();
+}
+
+template <int N, int DIM, bool FT>
+static hipError_t launch_fused_g(const EvalArgs& a, hipStream_t s, const Ext& ext, const DipoleArgs& dip) {
+    using Gm = Geo<N>;
+    cpx* const X = reinterpret_cast<cpx*>(DIM == 3 ? a.X2 : a.X1);
+    const cpx* const tw = reinterpret_cast<const cpx*>(DIM == 3 ? a.twz : a.twy);
+    const bool hint = (a.hint_bits >> 2) & 1;
+    const int np = DIM == 3 ? a.kxn * 2 * ext.ny : ext.nx + 1, kx0 = DIM == 3 ? a.kx0 : 0;
+    const unsigned nb = (unsigned)((fused_slots<N, DIM>(np) + Gm::PPZ - 1) / Gm::PPZ);
+    double* const ep = a.epart;
+    if constexpr (DIM == 3) {
+        if (a.dipolar) {
+            if (a.energy) {
+                if (hint) k_fused_g<N, 3, SPEC_DIPOLAR, NT_P3, true, FT><<<nb, Gm::TZ, 0, s>>>(X, a.spec, tw, np, kx0, dip, ext, ep);
+                else k_fused_g<N, 3, SPEC_DIPOLAR, 0, true, FT><<<nb, Gm::TZ, 0, s>>>(X, a.spec, tw, np, kx0, dip, ext, ep);
+            } else {
+                if (hint) k_fused_g<N, 3, SPEC_DIPOLAR, NT_P3, false, FT><<<nb, Gm::TZ, 0, s>>>(X, a.spec, tw, np, kx0, dip, ext);
+                else k_fused_g<N, 3, SPEC_DIPOLAR, 0, false, FT><<<nb, Gm::TZ, 0, s>>>(X, a.spec, tw, np, kx0, dip, ext);
+            }
+            return hipGetLastError();
+        }
+    }
+    if (a.energy) {
+        if (hint) k_fused_g<N, DIM, SPEC_PLAIN, NT_P3, true, FT><<<nb, Gm::TZ, 0, s>>>(X, a.spec, tw, np, kx0, dip, ext, ep);
+        else k_fused_g<N, DIM, SPEC_PLAIN, 0, true, FT><<<nb, Gm::TZ, 0, s>>>(X, a.spec, tw, np, kx0, dip, ext, ep);
+    } else {
+        if (hint) k_fused_g<N, DIM, SPEC_PLAIN, NT_P3, false, FT><<<nb, Gm::TZ, 0, s>>>(X, a.spec, tw, np, kx0, dip, ext);
+        else k_fused_g<N, DIM, SPEC_PLAIN, 0, false, FT><<<nb, Gm::TZ, 0, s>>>(X, a.spec, tw, np, kx0, dip, ext);
     }
     return hipGetLastError();
 }
@@ -389,11 +484,9 @@ hipError_t GS_CAT(launch_eval_g_, GS_N)(const EvalArgs& a, hipStream_t s, int pa
     ext.nx = a.nx;
     ext.ny = a.ny;
     ext.nz = a.d == 3 ? a.nz : 1;
-    cpx* const X1 = reinterpret_cast<cpx*>(a.X1);
-    cpx* const X2 = reinterpret_cast<cpx*>(a.X2);
-    const bool hint = (a.hint_bits >> (pass - 1)) & 1;
     if (pass == 1 || pass == 5) {
-        const hipError_t e = a.d == 2 ? launch_x_g<px_2d<N>(false)>(a, s, pass, ext) : launch_x_g<Gm::PPX>(a, s, pass, ext);
+        const hipError_t e = a.d == 2 ? launch_x_g<px_2d<N>(), p1_split_px<N>(2), px_2d<N>()>(a, s, pass, ext)
+                                      : launch_x_g<Gm::PPX, p1_split_px<N>(3), Gm::PPX>(a, s, pass, ext);
         if (e != hipSuccess || pass == 1 || !a.energy) return e;
         // the energy's pencil sums were written by the fused pass
         return launch_energy_total(a.epart, a.epencils, a.escale, a.energy, s);
@@ -406,55 +499,16 @@ hipError_t GS_CAT(launch_eval_g_, GS_N)(const EvalArgs& a, hipStream_t s, int pa
     }
     dip.nm_over_M = a.nm_over_M;
     if constexpr (N <= GS_MAX_N_3D) {
-      if (a.d == 3) {
-        const cpx* const twy = reinterpret_cast<const cpx*>(a.twy);
-        const dim3 gy((ext.nz + Gm::PPY - 1) / Gm::PPY, a.kxn);
-        if (pass == 2) {
-            if (hint) k_y_fwd_g<N, NT_P2><<<gy, Gm::TY, 0, s>>>(X1, X2, twy, a.kx0, ext);
-            else k_y_fwd_g<N, 0><<<gy, Gm::TY, 0, s>>>(X1, X2, twy, a.kx0, ext);
-        } else if (pass == 4) {
-            if (hint) k_y_inv_g<N, NT_P4><<<gy, Gm::TY, 0, s>>>(X2, X1, twy, a.kx0, ext);
-            else k_y_inv_g<N, 0><<<gy, Gm::TY, 0, s>>>(X2, X1, twy, a.kx0, ext);
-        } else if (pass == 3) {
-            const cpx* const twz = reinterpret_cast<const cpx*>(a.twz);
-            const int np = a.kxn * 2 * ext.ny;
-            const unsigned nb = (unsigned)((np + Gm::PPZ - 1) / Gm::PPZ);
-            double* const ep = a.epart;
-            if (a.dipolar) {
-                if (a.energy) {
-                    if (hint) k_fused_g<N, 3, SPEC_DIPOLAR, NT_P3, true><<<nb, Gm::TZ, 0, s>>>(X2, a.spec, twz, np, a.kx0, dip, ext, ep);
-                    else k_fused_g<N, 3, SPEC_DIPOLAR, 0, true><<<nb, Gm::TZ, 0, s>>>(X2, a.spec, twz, np, a.kx0, dip, ext, ep);
-                } else {
-                    if (hint) k_fused_g<N, 3, SPEC_DIPOLAR, NT_P3><<<nb, Gm::TZ, 0, s>>>(X2, a.spec, twz, np, a.kx0, dip, ext);
-                    else k_fused_g<N, 3, SPEC_DIPOLAR, 0><<<nb, Gm::TZ, 0, s>>>(X2, a.spec, twz, np, a.kx0, dip, ext);
-                }
-            } else {
-                if (a.energy) {
-                    if (hint) k_fused_g<N, 3, SPEC_PLAIN, NT_P3, true><<<nb, Gm::TZ, 0, s>>>(X2, a.spec, twz, np, a.kx0, dip, ext, ep);
-                    else k_fused_g<N, 3, SPEC_PLAIN, 0, true><<<nb, Gm::TZ, 0, s>>>(X2, a.spec, twz, np, a.kx0, dip, ext, ep);
-                } else {
-                    if (hint) k_fused_g<N, 3, SPEC_PLAIN, NT_P3><<<nb, Gm::TZ, 0, s>>>(X2, a.spec, twz, np, a.kx0, dip, ext);
-                    else k_fused_g<N, 3, SPEC_PLAIN, 0><<<nb, Gm::TZ, 0, s>>>(X2, a.spec, twz, np, a.kx0, dip, ext);
-                }
-            }
-        } else {
-            return hipErrorInvalidValue;
+        if (a.d == 3) {
+            if (pass == 2 || pass == 4)
+                return ext.nz % Gm::PPY == 0 ? launch_y_g<N, true>(a, s, pass, ext) : launch_y_g<N, false>(a, s, pass, ext);
+            if (pass != 3) return hipErrorInvalidValue;
+            return (2 * ext.ny) % Gm::PPZ == 0 ? launch_fused_g<N, 3, true>(a, s, ext, dip)
+                                               : launch_fused_g<N, 3, false>(a, s, ext, dip);
         }
-        return hipGetLastError();
-      }
     }
     if (pass != 3 || a.d != 2) return hipErrorInvalidValue;
-    const cpx* const twy = reinterpret_cast<const cpx*>(a.twy);
-    const int np = ext.nx + 1;
-    const unsigned nb = (unsigned)((fused_slots<N, 2>(np) + Gm::PPZ - 1) / Gm::PPZ);
-    if (a.energy) {
-        if (hint) k_fused_g<N, 2, SPEC_PLAIN, NT_P3, true><<<nb, Gm::TZ, 0, s>>>(X1, a.spec, twy, np, 0, dip, ext, a.epart);
-        else k_fused_g<N, 2, SPEC_PLAIN, 0, true><<<nb, Gm::TZ, 0, s>>>(X1, a.spec, twy, np, 0, dip, ext, a.epart);
-        return hipGetLastError();
-    }
-    if (hint) k_fused_g<N, 2, SPEC_PLAIN, NT_P3><<<nb, Gm::TZ, 0, s>>>(X1, a.spec, twy, np, 0, dip, ext);
-    else k_fused_g<N, 2, SPEC_PLAIN, 0><<<nb, Gm::TZ, 0, s>>>(X1, a.spec, twy, np, 0, dip, ext);
-    return hipGetLastError();
+    return launch_fused_g<N, 2, false>(a, s, ext, dip);
 }
 
 hipError_t GS_CAT(launch_eval_, GS_N)(const EvalArgs& a, hipStream_t s, int which) {

@@ -160,7 +160,9 @@ struct Ext {
 // XV: radix plan of the row transforms (XPlan).
 // EMB (with CUBE): the density is the first ext.nx x ext.ny x ext.nz points of the transform
 // grid, read from an array of those extents, zeros elsewhere (padding to B_3 without a copy).
-template <int N, int NT = NT_P1, bool CUBE = true, int PX = Geo<N>::PPX, int XV = 0, bool EMB = false>
+// FT (with CUBE = false): the rows are known to fill the tiles (ext.ny a multiple of twice the
+// default tile's pairs), so nothing is bounds-checked and the rows pair as on a cubic grid.
+template <int N, int NT = NT_P1, bool CUBE = true, int PX = Geo<N>::PPX, int XV = 0, bool EMB = false, bool FT = false>
 __device__ __forceinline__ void x_r2c_tile(gp<const double> __restrict__ rho, gp<cpx> __restrict__ X1,
                                            gp<const cpx> __restrict__ tw, int bx, int z, int tid, bool active,
                                            cpx* lds, Ext ext = Ext()) {
@@ -172,14 +174,14 @@ __device__ __forceinline__ void x_r2c_tile(gp<const double> __restrict__ rho, gp
     const int pB = tid % PP, tB = tid / PP;    // store role: consecutive y
     const int y0 = bx * 2 * PP;
     // rows beyond n exist only when 2 PPX does not divide n
-    constexpr bool FULL = CUBE && (N % (2 * PP) == 0);
+    constexpr bool FULL = CUBE ? N % (2 * PP) == 0 : FT;
     const bool okA = active && (FULL || (y0 + 2 * pA) < NY), okB = active && (FULL || (y0 + 2 * pB) < NY);
     // the two real rows of pair p: y0 + 16 (p / 8) + p % 8 and 8 rows further when the tile
     // divides the grid and holds a multiple of 8 pairs (each 16-byte store instruction on the
     // transposed X1 side then fills whole 128-byte lines: P1 at 256^3 0.0765 -> 0.0706 ms),
     // else y0 + 2p and y0 + 2p + 1
     // (the pairing follows the default tile, Geo<N>::PPX pairs, for every PX: the same bits)
-    constexpr bool SPLIT = FULL && Gm::PPX % 8 == 0 && N % (2 * Gm::PPX) == 0;
+    constexpr bool SPLIT = FULL && Gm::PPX % 8 == 0 && (!CUBE || N % (2 * Gm::PPX) == 0);
     constexpr int RS = SPLIT ? 8 : 1;
     const int qA = bx * PP + pA, rowA = SPLIT ? 16 * (qA / 8) + qA % 8 : 2 * qA;
     const int qB = bx * PP + pB, rowB = SPLIT ? 16 * (qB / 8) + qB % 8 : 2 * qB;
@@ -274,8 +276,9 @@ template <int N> constexpr int p1_split_px(int d) {
 // P1 of a cubic grid with the two halves of the padded transform (h = 0, 1) on the two 32-lane
 // halves of every wave, as x_c2r_tile_split: twice the threads and LDS areas per row pair, each
 // thread transforming, splitting and storing one half instead of both in turn.  The same
-// arithmetic per half as x_r2c_tile, so the same bits.  EMB as there.
-template <int N, int NT, int PX, bool EMB = false>
+// arithmetic per half as x_r2c_tile, so the same bits.  EMB as there; RECT: a grid whose axes have
+// their own n, ext.ny rows that fill the tiles.
+template <int N, int NT, int PX, bool EMB = false, bool RECT = false>
 __device__ __forceinline__ void x_r2c_tile_split(gp<const double> __restrict__ rho, gp<cpx> __restrict__ X1,
                                                  gp<const cpx> __restrict__ tw, int bx, int z, int tid, cpx* lds,
                                                  bool active = true, Ext ext = Ext()) {
@@ -287,14 +290,15 @@ __device__ __forceinline__ void x_r2c_tile_split(gp<const double> __restrict__ r
     const int tq = 32 * w + (l & 31);           // thread within its half
     const int tA = tq % G, pA = tq / G;         // load role: consecutive x
     const int pB = tq % PP, tB = tq / PP;       // store role: consecutive y
-    constexpr bool FULL = (N % (2 * PP) == 0);
-    constexpr bool SPLIT = FULL && Gm::PPX % 8 == 0 && N % (2 * Gm::PPX) == 0;
+    const int NY = RECT ? ext.ny : N;
+    constexpr bool FULL = RECT || N % (2 * PP) == 0;
+    constexpr bool SPLIT = FULL && Gm::PPX % 8 == 0 && (RECT || N % (2 * Gm::PPX) == 0);
     constexpr int RS = SPLIT ? 8 : 1;
     const int qA = bx * PP + pA, rowA = SPLIT ? 16 * (qA / 8) + qA % 8 : 2 * qA;
     const int qB = bx * PP + pB, rowB = SPLIT ? 16 * (qB / 8) + qB % 8 : 2 * qB;
-    const bool okA = active && (FULL || 2 * qA < N), okB = active && (FULL || 2 * qB < N);
+    const bool okA = active && (FULL || 2 * qA < NY), okB = active && (FULL || 2 * qB < NY);
     cpx v[E];
-    const int OX = EMB ? ext.nx : N, OY = EMB ? ext.ny : N;
+    const int OX = EMB ? ext.nx : N, OY = EMB ? ext.ny : NY;
     const bool r0 = okA && (!EMB || (z < ext.nz && rowA < ext.ny));
     const bool r1 = okA && (!EMB || (z < ext.nz && rowA + RS < ext.ny));
     gp<const double> ra = rho + ((size_t)z * OY + rowA) * OX;
@@ -312,7 +316,7 @@ __device__ __forceinline__ void x_r2c_tile_split(gp<const double> __restrict__ r
 #pragma unroll
     for (int e = 0; e < E; ++e) aB[lds_pad(tB + G * e)] = v[e];
     lds_barrier();
-    gp<cpx> out = X1 + (size_t)z * (N + 1) * N + rowB;
+    gp<cpx> out = X1 + (size_t)z * (N + 1) * NY + rowB;
 #pragma unroll
     for (int e = 0; e <= E / 2; ++e) {
         if (e == E / 2 && !(h == 0 && tB == 0)) continue;
@@ -323,7 +327,7 @@ __device__ __forceinline__ void x_r2c_tile_split(gp<const double> __restrict__ r
             const cpx sa = cmk(0.5 * (zk.x + zp.x), 0.5 * (zk.y - zp.y));       // (Z + conj P)/2
             const cpx df = cmk(zk.x - zp.x, zk.y + zp.y);                        //  Z - conj P
             const cpx sb = cmk(0.5 * df.y, -0.5 * df.x);                         // /(2i)
-            gp<cpx> o = out + (size_t)(2 * k + h) * N;
+            gp<cpx> o = out + (size_t)(2 * k + h) * NY;
             stg<(NT & 2) != 0>(o, sa);
             stg<(NT & 2) != 0>(o + RS, sb);
         }
@@ -346,8 +350,9 @@ __global__ void __launch_bounds__((2 * PX * Geo<N>::G)) k_x_r2c_split(const doub
 // EMB (with CUBE): the potential is stored for the first ext.nx x ext.ny x ext.nz points of the
 // transform grid only, into an array of those extents (padding to B_3 without a copy).
 // HV (with CUBE): X1 holds two halves whose sum is the input (x_c2r_tile_split).
+// FT (with CUBE = false): whole tiles, as in x_r2c_tile.
 template <int N, int NT = NT_P5, bool SC = false, bool CUBE = true, int PX = Geo<N>::PPX, int XV = 0,
-          bool EMB = false, bool HV = false>
+          bool EMB = false, bool HV = false, bool FT = false>
 __device__ __forceinline__ void x_c2r_tile(gp<const cpx> __restrict__ X1, gp<double> u,
                                            gp<const cpx> __restrict__ tw, int bx, int z, int tid, bool active,
                                            cpx* lds, Ext ext = Ext(), double oscale = 1.0) {
@@ -359,12 +364,12 @@ __device__ __forceinline__ void x_c2r_tile(gp<const cpx> __restrict__ X1, gp<dou
     const int pB = tid % PP, tB = tid / PP;    // load role: consecutive y
     const int y0 = bx * 2 * PP;
     // rows beyond n exist only when 2 PPX does not divide n
-    constexpr bool FULL = CUBE && (N % (2 * PP) == 0);
+    constexpr bool FULL = CUBE ? N % (2 * PP) == 0 : FT;
     const bool okA = active && (FULL || (y0 + 2 * pA) < NY), okB = active && (FULL || (y0 + 2 * pB) < NY);
     // rows of pair p as in x_r2c_tile (8 rows apart in groups of 16 when the tile divides the
     // grid and holds a multiple of 8 pairs: whole 128-byte lines per load instruction on the
     // transposed X1 side)
-    constexpr bool SPLIT = FULL && Gm::PPX % 8 == 0 && N % (2 * Gm::PPX) == 0;
+    constexpr bool SPLIT = FULL && Gm::PPX % 8 == 0 && (!CUBE || N % (2 * Gm::PPX) == 0);
     constexpr int RS = SPLIT ? 8 : 1;
     const int qA = bx * PP + pA, rowA = SPLIT ? 16 * (qA / 8) + qA % 8 : 2 * qA;
     const int qB = bx * PP + pB, rowB = SPLIT ? 16 * (qB / 8) + qB % 8 : 2 * qB;
@@ -453,7 +458,8 @@ template <int N, int PX, int XV = 0> constexpr int p5_threads() {
 
 // HV: X1 holds the two halves k_plane leaves (the second one (N + 1) N N values on), whose sum
 // is the transform's input.
-template <int N, int NT, bool SC, int PX, int XV = 0, bool EMB = false, bool HV = false>
+// RECT: as in x_r2c_tile_split.
+template <int N, int NT, bool SC, int PX, int XV = 0, bool EMB = false, bool HV = false, bool RECT = false>
 __device__ __forceinline__ void x_c2r_tile_split(gp<const cpx> __restrict__ X1, gp<double> u,
                                                  gp<const cpx> __restrict__ tw, int bx, int z, int tid, cpx* lds,
                                                  double oscale, bool active = true, Ext ext = Ext()) {
@@ -466,13 +472,14 @@ __device__ __forceinline__ void x_c2r_tile_split(gp<const cpx> __restrict__ X1, 
     const int tA = tq % G, pA = tq / G;         // store role: consecutive x
     const int pB = tq % PP, tB = tq / PP;       // load role: consecutive y
     const int y0 = bx * 2 * PP;
-    constexpr bool FULL = (N % (2 * PP) == 0);
-    const bool okA = active && (FULL || (y0 + 2 * pA) < N), okB = active && (FULL || (y0 + 2 * pB) < N);
-    constexpr bool SPLIT = FULL && Gm::PPX % 8 == 0 && N % (2 * Gm::PPX) == 0;
+    const int NY = RECT ? ext.ny : N;
+    constexpr bool FULL = RECT || N % (2 * PP) == 0;
+    const bool okA = active && (FULL || (y0 + 2 * pA) < NY), okB = active && (FULL || (y0 + 2 * pB) < NY);
+    constexpr bool SPLIT = FULL && Gm::PPX % 8 == 0 && (RECT || N % (2 * Gm::PPX) == 0);
     constexpr int RS = SPLIT ? 8 : 1;
     const int qA = bx * PP + pA, rowA = SPLIT ? 16 * (qA / 8) + qA % 8 : 2 * qA;
     const int qB = bx * PP + pB, rowB = SPLIT ? 16 * (qB / 8) + qB % 8 : 2 * qB;
-    gp<const cpx> in = X1 + (size_t)z * (N + 1) * N + rowB;
+    gp<const cpx> in = X1 + (size_t)z * (N + 1) * NY + rowB;
     cpx v[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) {
@@ -481,7 +488,7 @@ __device__ __forceinline__ void x_c2r_tile_split(gp<const cpx> __restrict__ X1, 
         const int mm = direct ? m : 2 * N - m;
         cpx a = cmk(0.0, 0.0), b = cmk(0.0, 0.0);
         if (okB) {
-            gp<const cpx> p = in + (size_t)mm * N;
+            gp<const cpx> p = in + (size_t)mm * NY;
             a = ldg<NT & 1>(p);
             b = ldg<NT & 1>(p + RS);
             if constexpr (HV) {
@@ -494,7 +501,7 @@ __device__ __forceinline__ void x_c2r_tile_split(gp<const cpx> __restrict__ X1, 
     }
     fft_t<Fx, true>(v, tA, lds + (h * PP + pA) * A, tB, lds + (h * PP + pB) * A, tw, h);
     // EMB: only the first ext.nx x ext.ny x ext.nz points, into an array of those extents
-    const int OX = EMB ? ext.nx : N, OY = EMB ? ext.ny : N;
+    const int OX = EMB ? ext.nx : N, OY = EMB ? ext.ny : NY;
     const bool r0 = okA && (!EMB || (z < ext.nz && rowA < ext.ny));
     const bool r1 = okA && (!EMB || (z < ext.nz && rowA + RS < ext.ny));
     gp<double> ua = u + ((size_t)z * OY + rowA) * OX;
@@ -572,7 +579,8 @@ __global__ void __launch_bounds__((p5_threads<N, Geo<N>::PPX>())) k_x_c2r_emb(co
 // ---------------------------------------------------------------------------
 // PY: z-pencils per block (a tile-shape variant: the same bits for every PY)
 // YV: radix plan of the pencil transforms (XPlan, as for the x passes)
-template <int N, int NT = NT_P2, bool CUBE = true, int PY = Geo<N>::PPY, int YV = 0>
+// FT (with CUBE = false): ext.nz is a multiple of PY, so nothing is bounds-checked
+template <int N, int NT = NT_P2, bool CUBE = true, int PY = Geo<N>::PPY, int YV = 0, bool FT = false>
 __device__ __forceinline__ void y_fwd_tile(gp<const cpx> __restrict__ X1, gp<cpx> __restrict__ X2,
                                            gp<const cpx> __restrict__ tw, int kx0, int bx, int kxl, int tid,
                                            bool active, cpx* lds, Ext ext = Ext()) {
@@ -585,7 +593,7 @@ __device__ __forceinline__ void y_fwd_tile(gp<const cpx> __restrict__ X1, gp<cpx
     const int kx = kx0 + kxl;                         // slab-local and global kx
     const int z0 = bx * PP;
     // z beyond n exists only when PPY does not divide n
-    constexpr bool FULL = CUBE && (N % PP == 0);
+    constexpr bool FULL = CUBE ? N % PP == 0 : FT;
     const bool okA = active && (FULL || (z0 + pA) < NZ), okB = active && (FULL || (z0 + pB) < NZ);
 
     cpx x[E];
@@ -621,7 +629,7 @@ __global__ void __launch_bounds__((PY * GeoX<N, YV>::G)) k_y_fwd(const cpx* __re
 // ---------------------------------------------------------------------------
 // P4: y-direction inverse with cropping.  Block = one kx, PPY consecutive z.
 // ---------------------------------------------------------------------------
-template <int N, int NT = NT_P4, bool CUBE = true, int PY = Geo<N>::PPY, int YV = 0>
+template <int N, int NT = NT_P4, bool CUBE = true, int PY = Geo<N>::PPY, int YV = 0, bool FT = false>
 __device__ __forceinline__ void y_inv_tile(gp<const cpx> __restrict__ X2, gp<cpx> __restrict__ X1,
                                            gp<const cpx> __restrict__ tw, int kx0, int bx, int kxl, int tid,
                                            bool active, cpx* lds, Ext ext = Ext()) {
@@ -634,7 +642,7 @@ __device__ __forceinline__ void y_inv_tile(gp<const cpx> __restrict__ X2, gp<cpx
     const int kx = kx0 + kxl;
     const int z0 = bx * PP;
     // z beyond n exists only when PPY does not divide n
-    constexpr bool FULL = CUBE && (N % PP == 0);
+    constexpr bool FULL = CUBE ? N % PP == 0 : FT;
     const bool okA = active && (FULL || (z0 + pA) < NZ), okB = active && (FULL || (z0 + pB) < NZ);
     gp<const cpx> src = X2 + (size_t)kxl * 2 * N * NZ + z0 + pB;
 
@@ -665,6 +673,51 @@ __global__ void __launch_bounds__((PY * GeoX<N, YV>::G)) k_y_inv(const cpx* __re
     __shared__ cpx lds[PY * Geo<N>::A];
     y_inv_tile<N, NT, true, PY, YV>((gp<const cpx>)X2, (gp<cpx>)X1, (gp<const cpx>)tw, kx0,
                                     die_tile<die_run<N>(N / PY, PY == 8 ? 2 : 1)>(blockIdx.x, gridDim.x), blockIdx.y, threadIdx.x, true, lds);
+}
+
+// P4 of a cubic grid with the two halves of the padded inverse on the two 32-lane halves of every
+// wave (as x_c2r_tile_split): each thread loads and transforms one half, and the halves' sums are
+// formed by a lane swap, each lane storing half of the pencil's values.  The same sums as
+// y_inv_tile, so the same bits.  Taken at n = 96, whose pass is too short for its waves to hide
+// a chain of two transforms (alone 9.97 -> 8.96, the evaluation 52.7 -> 51.4 us); at 80 the
+// evaluation takes 42.7 us with it and 40.4 without, from 112 on the pass takes the same time.
+template <int N> constexpr bool p4_split() { return N > 80 && N < 112; }
+template <int N, int NT, int PY>
+__device__ __forceinline__ void y_inv_tile_split(gp<const cpx> __restrict__ X2, gp<cpx> __restrict__ X1,
+                                                 gp<const cpx> __restrict__ tw, int kx0, int bx, int kxl, int tid,
+                                                 cpx* lds) {
+    using Gm = Geo<N>;
+    using Fy = typename Gm::F;
+    constexpr int E = Fy::E, G = Fy::G, PP = PY, A = Gm::A;
+    static_assert((PY * G) % 32 == 0, "whole half-waves");
+    const int w = tid >> 6, l = tid & 63, h = l >> 5;
+    const int tq = 32 * w + (l & 31);
+    const int tA = tq % G, pA = tq / G;        // store role: consecutive y
+    const int pB = tq % PP, tB = tq / PP;      // load role: consecutive z
+    const int kx = kx0 + kxl, z0 = bx * PP;
+    constexpr bool FULL = N % PP == 0;
+    const bool okA = FULL || (z0 + pA) < N, okB = FULL || (z0 + pB) < N;
+    gp<const cpx> src = X2 + (size_t)kxl * 2 * N * N + z0 + pB;
+    cpx v[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) v[e] = okB ? ldg<NT & 1>(src + (size_t)(2 * (tB + G * e) + h) * N) : cmk(0.0, 0.0);
+    fft_t<Fy, true>(v, tA, lds + (h * PP + pA) * A, tB, lds + (h * PP + pB) * A, tw, h);
+    gp<cpx> dst = X1 + ((size_t)(z0 + pA) * (N + 1) + kx) * N;
+#pragma unroll
+    for (int e = 0; e < E / 2; ++e) {
+        cpx a = v[e], b = v[e + E / 2];
+        swap_halves(a, b);
+        if (okA) stg<(NT & 2) != 0>(dst + tA + G * (h * (E / 2) + e), cadd(a, b));
+    }
+}
+
+template <int N, int NT, int PY>
+__global__ void __launch_bounds__((2 * PY * Geo<N>::G)) k_y_inv_split(const cpx* __restrict__ X2, cpx* __restrict__ X1,
+                                                                     const cpx* __restrict__ tw, int kx0) {
+    __shared__ cpx lds[2 * PY * Geo<N>::A];
+    y_inv_tile_split<N, NT, PY>((gp<const cpx>)X2, (gp<cpx>)X1, (gp<const cpx>)tw, kx0,
+                                die_tile<die_run<N>(N / PY, PY == 8 ? 2 : 1)>(blockIdx.x, gridDim.x), blockIdx.y,
+                                threadIdx.x, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -1007,8 +1060,9 @@ __device__ __forceinline__ void fused_body_pack(gp<cpx> __restrict__ X, gp<const
 // One pencil group of the fused pass without prefetch (the batched launches).
 // PZ: pencils per block (a tile-shape variant: the same bits for every PZ); RV: radix plan
 // (FusedPlan)
+// FT (with CUBE = false): the pencils fill the groups
 template <int N, int DIM, int MODE, int NT = NT_P3, bool CUBE = true, int PZ = Geo<N>::PPZ, bool EN = false,
-          int RV = 0>
+          int RV = 0, bool FT = false>
 __device__ __forceinline__ void fused_group(gp<cpx> __restrict__ X, gp<const double> __restrict__ spec,
                                             gp<const cpx> __restrict__ tw, int npencils, int kx0,
                                             const DipoleArgs& dip, int g, int tid, bool active, cpx* lds,
@@ -1022,7 +1076,7 @@ __device__ __forceinline__ void fused_group(gp<cpx> __restrict__ X, gp<const dou
     const int slot = g * PP + pl;
     // in 3D the pencil count is a multiple of 2n, so groups of PP pencils never run past it
     // when PP divides 2n; 2D has n + 1 pencils (n slots when pencils 0 and n ride together)
-    constexpr bool FULL = CUBE && (DIM == 3 && (2 * N) % PP == 0);
+    constexpr bool FULL = CUBE ? DIM == 3 && (2 * N) % PP == 0 : FT;
     const bool ok = active && (FULL || slot < fused_slots<N, DIM, RV>(npencils));
     const int pencil = ok ? fused_pencil<N, DIM>(slot, NY) : 0;
     cpx v[E];
@@ -1179,52 +1233,84 @@ __global__ void __launch_bounds__((GeoP<N>::T)) k_plane(const cpx* __restrict__ 
 // ---------------------------------------------------------------------------
 // The passes on grids whose axes have their own n (Section 2.5 with per-axis n_j): the
 // transform length N is the n of the axis the pass transforms, the other extents come in
-// `ext`, and every row and pencil is bounds-checked.  One block per tile or pencil group.
+// `ext`.  FT: the other extents fill the pass's tiles (the launch looks), so it runs the cubic
+// passes' unchecked code, row pairs and split forms; otherwise every row and pencil is
+// bounds-checked.  One block per tile or pencil group.
 // ---------------------------------------------------------------------------
-template <int N, int NT, int PX = Geo<N>::PPX>
+// Tiles that share a 128-byte line of X1 (line_tiles): the row pairs are split on whole tiles only.
+template <int N, int PX, bool FT> constexpr int line_tiles_g() {
+    constexpr int run = FT && Geo<N>::PPX % 8 == 0 ? 16 * PX : 32 * PX;
+    return run >= 128 ? 1 : 128 / run;
+}
+
+template <int N, int NT, int PX = Geo<N>::PPX, bool FT = false>
 __global__ void __launch_bounds__((PX * Geo<N>::G)) k_x_r2c_g(const double* __restrict__ rho, cpx* __restrict__ X1,
                                                               const cpx* __restrict__ tw, Ext ext) {
     __shared__ cpx lds[PX * Geo<N>::A];
-    x_r2c_tile<N, NT, false, PX>((gp<const double>)rho, (gp<cpx>)X1, (gp<const cpx>)tw,
-                                 die_tile<(PX < 4 ? 4 / PX : 1)>(blockIdx.x, gridDim.x), blockIdx.y,
-                             threadIdx.x, true, lds, ext);
+    x_r2c_tile<N, NT, false, PX, 0, false, FT>((gp<const double>)rho, (gp<cpx>)X1, (gp<const cpx>)tw,
+                                               die_tile<line_tiles_g<N, PX, FT>()>(blockIdx.x, gridDim.x), blockIdx.y,
+                                               threadIdx.x, true, lds, ext);
 }
 
-template <int N, int NT, bool SC, int PX = Geo<N>::PPX>
+template <int N, int NT, bool SC, int PX = Geo<N>::PPX, bool FT = false>
 __global__ void __launch_bounds__((PX * Geo<N>::G)) k_x_c2r_g(const cpx* __restrict__ X1, double* u,
                                                               const cpx* __restrict__ tw, Ext ext, double oscale) {
     __shared__ cpx lds[PX * Geo<N>::A];
-    x_c2r_tile<N, NT, SC, false, PX>((gp<const cpx>)X1, (gp<double>)u, (gp<const cpx>)tw,
-                                     die_tile<(PX < 4 ? 4 / PX : 1)>(blockIdx.x, gridDim.x), blockIdx.y,
-                                 threadIdx.x, true, lds, ext, oscale);
+    x_c2r_tile<N, NT, SC, false, PX, 0, false, false, FT>((gp<const cpx>)X1, (gp<double>)u, (gp<const cpx>)tw,
+                                                          die_tile<line_tiles_g<N, PX, FT>()>(blockIdx.x, gridDim.x),
+                                                          blockIdx.y, threadIdx.x, true, lds, ext, oscale);
 }
 
-template <int N, int NT>
+// The same with the halves on the lane halves, for rows that fill the tiles.
+template <int N, int NT, int PX>
+__global__ void __launch_bounds__((2 * PX * Geo<N>::G)) k_x_r2c_g_split(const double* __restrict__ rho,
+                                                                       cpx* __restrict__ X1,
+                                                                       const cpx* __restrict__ tw, Ext ext) {
+    __shared__ cpx lds[2 * PX * Geo<N>::A];
+    x_r2c_tile_split<N, NT, PX, false, true>((gp<const double>)rho, (gp<cpx>)X1, (gp<const cpx>)tw,
+                                             die_tile<line_tiles_g<N, PX, true>()>(blockIdx.x, gridDim.x), blockIdx.y,
+                                             threadIdx.x, lds, true, ext);
+}
+
+template <int N, int NT, bool SC, int PX>
+__global__ void __launch_bounds__((2 * PX * Geo<N>::G)) k_x_c2r_g_split(const cpx* __restrict__ X1, double* u,
+                                                                       const cpx* __restrict__ tw, Ext ext,
+                                                                       double oscale) {
+    __shared__ cpx lds[2 * PX * Geo<N>::A];
+    x_c2r_tile_split<N, NT, SC, PX, 0, false, false, true>((gp<const cpx>)X1, (gp<double>)u, (gp<const cpx>)tw,
+                                                           die_tile<line_tiles_g<N, PX, true>()>(blockIdx.x, gridDim.x),
+                                                           blockIdx.y, threadIdx.x, lds, oscale, true, ext);
+}
+
+template <int N, int NT, bool FT>
 __global__ void __launch_bounds__(Geo<N>::TY) k_y_fwd_g(const cpx* __restrict__ X1, cpx* __restrict__ X2,
                                                         const cpx* __restrict__ tw, int kx0, Ext ext) {
     __shared__ cpx lds[Geo<N>::PPY * Geo<N>::A];
-    y_fwd_tile<N, NT, false>((gp<const cpx>)X1, (gp<cpx>)X2, (gp<const cpx>)tw, kx0, blockIdx.x, blockIdx.y,
-                             threadIdx.x, true, lds, ext);
+    y_fwd_tile<N, NT, false, Geo<N>::PPY, 0, FT>((gp<const cpx>)X1, (gp<cpx>)X2, (gp<const cpx>)tw, kx0,
+                                                 die_tile<(Geo<N>::PPY == 8 ? 2 : 1)>(blockIdx.x, gridDim.x),
+                                                 blockIdx.y, threadIdx.x, true, lds, ext);
 }
 
-template <int N, int NT>
+template <int N, int NT, bool FT>
 __global__ void __launch_bounds__(Geo<N>::TY) k_y_inv_g(const cpx* __restrict__ X2, cpx* __restrict__ X1,
                                                         const cpx* __restrict__ tw, int kx0, Ext ext) {
     __shared__ cpx lds[Geo<N>::PPY * Geo<N>::A];
-    y_inv_tile<N, NT, false>((gp<const cpx>)X2, (gp<cpx>)X1, (gp<const cpx>)tw, kx0, blockIdx.x, blockIdx.y,
-                             threadIdx.x, true, lds, ext);
+    y_inv_tile<N, NT, false, Geo<N>::PPY, 0, FT>((gp<const cpx>)X2, (gp<cpx>)X1, (gp<const cpx>)tw, kx0,
+                                                 die_tile<(Geo<N>::PPY == 8 ? 2 : 1)>(blockIdx.x, gridDim.x),
+                                                 blockIdx.y, threadIdx.x, true, lds, ext);
 }
 
-template <int N, int DIM, int MODE, int NT, bool EN = false>
+template <int N, int DIM, int MODE, int NT, bool EN = false, bool FT = false>
 __global__ void __launch_bounds__(Geo<N>::TZ) k_fused_g(cpx* __restrict__ Xg, const double* __restrict__ specg,
                                                         const cpx* __restrict__ twg, int npencils, int kx0,
                                                         DipoleArgs dip, Ext ext, double* __restrict__ part = nullptr) {
     __shared__ cpx lds[Geo<N>::PPZ * 2 * Geo<N>::AZ];
     const int ngroups = (fused_slots<N, DIM>(npencils) + Geo<N>::PPZ - 1) / Geo<N>::PPZ;
     if ((int)blockIdx.x < ngroups)
-        fused_group<N, DIM, MODE, NT, false, Geo<N>::PPZ, EN>((gp<cpx>)Xg, (gp<const double>)specg,
-                                                              (gp<const cpx>)twg, npencils, kx0, dip, blockIdx.x,
-                                                              threadIdx.x, true, lds, ext, (gp<double>)part);
+        fused_group<N, DIM, MODE, NT, false, Geo<N>::PPZ, EN, 0, FT>((gp<cpx>)Xg, (gp<const double>)specg,
+                                                                     (gp<const cpx>)twg, npencils, kx0, dip,
+                                                                     die_tile<(DIM == 3 && Geo<N>::PPZ == 1 ? 2 : 1)>(blockIdx.x, ngroups),
+                                                                     threadIdx.x, true, lds, ext, (gp<double>)part);
 }
 
 }  // namespace gsk
