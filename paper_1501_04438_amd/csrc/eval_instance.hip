@@ -450,7 +450,12 @@ static hipError_t launch_fused_g(const EvalArgs& a, hipStream_t s, const Ext& ex
     const cpx* const tw = reinterpret_cast<const cpx*>(DIM == 3 ? a.twz : a.twy);
     const bool hint = (a.hint_bits >> 2) & 1;
     const int np = DIM == 3 ? a.kxn * 2 * ext.ny : ext.nx + 1, kx0 = DIM == 3 ? a.kx0 : 0;
-    const unsigned nb = (unsigned)((fused_slots<N, DIM>(np) + Gm::PPZ - 1) / Gm::PPZ);
+    const int groups = (fused_slots<N, DIM>(np) + Gm::PPZ - 1) / Gm::PPZ;
+    unsigned nb = (unsigned)groups;
+    if constexpr (gs_fused_persistent_g(DIM, N)) {
+        static const int cap = resident_blocks((const void*)k_fused_g<N, DIM, SPEC_PLAIN, 0, false, FT>, Gm::TZ);
+        nb = fused_grid(groups, cap, a.fused_grid_mult);
+    }
     double* const ep = a.epart;
     if constexpr (DIM == 3) {
         if (a.dipolar) {

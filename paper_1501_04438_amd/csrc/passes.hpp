@@ -1116,8 +1116,8 @@ __global__ void __launch_bounds__((PZ * 2 * GeoZ<N, RV>::GZ)) k_fused(cpx* __res
     } else {
         for (int g = blockIdx.x; g < ngroups; g += gridDim.x)
             fused_group<N, DIM, MODE, NT, true, PZ, EN, RV>((gp<cpx>)Xg, (gp<const double>)specg, (gp<const cpx>)twg,
-                                                            npencils, kx0, dip, g, threadIdx.x, true, lds, Ext(),
-                                                            (gp<double>)part);
+                                                            npencils, kx0, dip, die_tile<PAIR>(g, ngroups), threadIdx.x,
+                                                            true, lds, Ext(), (gp<double>)part);
     }
 }
 
@@ -1306,11 +1306,17 @@ __global__ void __launch_bounds__(Geo<N>::TZ) k_fused_g(cpx* __restrict__ Xg, co
                                                         DipoleArgs dip, Ext ext, double* __restrict__ part = nullptr) {
     __shared__ cpx lds[Geo<N>::PPZ * 2 * Geo<N>::AZ];
     const int ngroups = (fused_slots<N, DIM>(npencils) + Geo<N>::PPZ - 1) / Geo<N>::PPZ;
-    if ((int)blockIdx.x < ngroups)
-        fused_group<N, DIM, MODE, NT, false, Geo<N>::PPZ, EN, 0, FT>((gp<cpx>)Xg, (gp<const double>)specg,
-                                                                     (gp<const cpx>)twg, npencils, kx0, dip,
-                                                                     die_tile<(DIM == 3 && Geo<N>::PPZ == 1 ? 2 : 1)>(blockIdx.x, ngroups),
-                                                                     threadIdx.x, true, lds, ext, (gp<double>)part);
+    constexpr int PAIR = DIM == 3 && Geo<N>::PPZ == 1 ? 2 : 1;
+    auto group = [&](int g) {
+        fused_group<N, DIM, MODE, NT, false, Geo<N>::PPZ, EN, 0, FT>(
+            (gp<cpx>)Xg, (gp<const double>)specg, (gp<const cpx>)twg, npencils, kx0, dip, die_tile<PAIR>(g, ngroups),
+            threadIdx.x, true, lds, ext, (gp<double>)part);
+    };
+    if constexpr (gs_fused_persistent_g(DIM, N)) {
+        for (int g = blockIdx.x; g < ngroups; g += gridDim.x) group(g);
+    } else {
+        if ((int)blockIdx.x < ngroups) group(blockIdx.x);
+    }
 }
 
 }  // namespace gsk

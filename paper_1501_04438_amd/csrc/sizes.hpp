@@ -7,13 +7,18 @@
 #define GS_MAX_N_3D 1024
 
 // Grid of the fused pass: persistent (rounds of co-resident blocks looping over pencil
-// groups, the per-thread stage twiddles kept in registers across groups) only for 3D
-// grids of n = 256; one block per pencil group elsewhere, where the twiddles held across
-// groups cost occupancy.  Measured fused-pass times, persistent -> one block per group:
-// 256^3 0.275 -> 0.295 ms (dipolar 0.320 -> 0.325); 192^3 0.172 -> 0.158; dipolar 128^3
-// 0.051 -> 0.048; 512^3 2.64 -> 2.45; 1024^3 26.2 -> 25.0; 2D 2048^2 0.077 -> 0.059 ms;
-// Coulomb 64^3 to 128^3 equal within the spread between runs.
-constexpr bool gs_fused_persistent(int d, int n) { return d == 3 && n == 256; }
+// groups, the per-thread stage twiddles kept in registers across groups) for 3D cubic grids of
+// n = 256, 384, 512, 640 and 768; one block per pencil group elsewhere, where the twiddles held across
+// groups cost occupancy.  Whole evaluations, one block per group -> persistent: 256^3 651 ->
+// 620, 384^3 2766 -> 2665, 512^3 5874 -> 5809 us, 640^3 16.4 -> 15.5, 768^3 25.6 -> 25.4 ms, but 160^3 200 -> 203, 320^3 1610 ->
+// 1682, dipolar 128^3 87.2 -> 88.6 us, 1024^3 57.2 -> 58.2 ms; 96^3, 128^3 and 192^3 equal.
+constexpr bool gs_fused_persistent(int d, int n) { return d == 3 && (n == 256 || n == 384 || n == 512 || n == 640 || n == 768); }
+// The same on grids whose axes differ, by the length of the fused axis: 128x256x512 (z first) 648
+// -> 634, 512x256x128 688 -> 656, 192x256x224 463 -> 450, 96x160x128 equal, but 224x320x192 (28
+// values per thread) 658 -> 759 us.
+constexpr bool gs_fused_persistent_g(int d, int n) {
+    return d == 3 && (n == 128 || n == 192 || n == 256 || n == 384 || n == 512);
+}
 
 // Lengths for which the cubic passes are also compiled in tile-shape variants (more or fewer
 // rows or pencils per block; the same bits) that the plan autotuner chooses among.
