@@ -231,7 +231,10 @@ __global__ void __launch_bounds__(BATCH_THREADS) k_batch_size(const BatchProblem
 // Memory ordering, local queues: the producer's stores reach the die's L2 before
 // its counter increment (every wave waits for its stores before the block barrier;
 // the vector L1 is write through), and a consumer invalidates its own L1 after
-// observing the counter.
+// observing the counter.  (At agent scope, sc1: the workgroup-scope form, sc0, leaves lines of
+// this CU's L1 that other CUs have since written; seen as stale values in a kernel that rewrote a
+// small buffer at short intervals.  A batch of 20 problems up to 128^3:
+// queue 944 -> 958 us.)
 // Otherwise agent-scope release (L2 write-back) and acquire (L2 invalidate).
 //
 // A dependency wait gives up after spin_limit polls (far beyond any task's
@@ -278,7 +281,7 @@ __global__ void __launch_bounds__(BATCH_THREADS) __attribute__((amdgpu_waves_per
                     }
                     __builtin_amdgcn_s_sleep(2);
                 }
-                if (Q.local) asm volatile("buffer_inv sc0" ::: "memory");        // this CU's L1
+                if (Q.local) asm volatile("buffer_inv sc1" ::: "memory");        // this CU's L1
                 else __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
             }
             s_next = (int)__builtin_amdgcn_readfirstlane(nx);
