@@ -270,7 +270,7 @@ static hipError_t launch_fused_v(const EvalArgs& a, hipStream_t s, const DipoleA
         const int capf = a.max_blocks_fused > 0 ? a.max_blocks_fused : cap3;
         const int np = a.kxn * 2 * N;
         const int groups = (np + PZ - 1) / PZ;
-        const unsigned nb = gs_fused_persistent(3, N) ? fused_grid(groups, capf, a.fused_grid_mult) : (unsigned)groups;
+        const unsigned nb = gs_fused_persistent(3, N, a.dipolar) ? fused_grid(groups, capf, a.fused_grid_mult) : (unsigned)groups;
         if constexpr (ETILE) {
             if (a.energy) {
                 // with the energy sum of every pencil (the default tile only)
@@ -294,7 +294,7 @@ static hipError_t launch_fused_v(const EvalArgs& a, hipStream_t s, const DipoleA
         return hipGetLastError();
       }
     }
-    static_assert(!gs_fused_persistent(2, N), "the 2D fused pass runs one block per pencil group");
+    static_assert(!gs_fused_persistent(2, N, false), "the 2D fused pass runs one block per pencil group");
     cpx* const X1 = reinterpret_cast<cpx*>(a.X1);
     const int np = N + 1;
     const unsigned nb = (unsigned)((fused_slots<N, 2, RV>(np) + PZ - 1) / PZ);
@@ -371,7 +371,8 @@ int GS_CAT(tile_variants_, GS_N)() {
 // The x passes of a grid whose axes have their own n: where the rows fill the tiles (a multiple of
 // twice the default tile's pairs, so that they pair as on a cubic grid) the cubic passes' forms,
 // PF (forward, 0: not split) and PI (inverse) row pairs per block; otherwise the bounds-checked
-// tile of PX pairs.  128 x 256 x 512: forward 92.9 -> 71, inverse 101.5 -> 82 us.
+// tile of PX pairs.  Whole evaluations, bounds-checked -> whole tiles in all passes: 96x160x128 109 ->
+// 92, 24x320x112 78 -> 61, 512x256x128 744 -> 698 us.
 template <int PX, int PF, int PI>
 static hipError_t launch_x_g(const EvalArgs& a, hipStream_t s, int pass, const Ext& ext) {
     constexpr int N = GS_N, G = Geo<N>::G, P0 = Geo<N>::PPX;
@@ -452,7 +453,7 @@ static hipError_t launch_fused_g(const EvalArgs& a, hipStream_t s, const Ext& ex
     const int np = DIM == 3 ? a.kxn * 2 * ext.ny : ext.nx + 1, kx0 = DIM == 3 ? a.kx0 : 0;
     const int groups = (fused_slots<N, DIM>(np) + Gm::PPZ - 1) / Gm::PPZ;
     unsigned nb = (unsigned)groups;
-    if constexpr (gs_fused_persistent_g(DIM, N)) {
+    if (gs_fused_persistent_g(DIM, N, a.dipolar)) {
         static const int cap = resident_blocks((const void*)k_fused_g<N, DIM, SPEC_PLAIN, 0, false, FT>, Gm::TZ);
         nb = fused_grid(groups, cap, a.fused_grid_mult);
     }

@@ -317,7 +317,8 @@ struct FftPlan {
     static constexpr int R[4] = {R0_, R1_, R2_, R3_};
 };
 
-// Default plans (few stages: one LDS exchange for n <= 256).
+// Default plans: few stages, so few LDS exchanges, and the values per thread that the measured
+// passes ran fastest with.
 template <int N> struct FftCfg;
 template <> struct FftCfg<8> : FftPlan<8, 4, 2, 4, 2> {};
 template <> struct FftCfg<12> : FftPlan<12, 6, 2, 6, 2> {};
@@ -337,7 +338,8 @@ template <> struct FftCfg<2048> : FftPlan<2048, 16, 3, 16, 16, 8> {};
 template <> struct FftCfg<384> : FftPlan<384, 12, 4, 4, 4, 4, 6> {};
 template <> struct FftCfg<768> : FftPlan<768, 12, 4, 4, 4, 4, 12> {};
 template <> struct FftCfg<1536> : FftPlan<1536, 24, 3, 8, 8, 24> {};
-// 5-smooth and 7-smooth lengths: 20 or 28 values per thread
+// 5-smooth and 7-smooth lengths: 10 or 20, 14 or 28 values per thread, the odd factor in the
+// largest radix where that saves a stage
 template <> struct FftCfg<20> : FftPlan<20, 10, 2, 10, 2> {};
 template <> struct FftCfg<40> : FftPlan<40, 10, 3, 10, 2, 2> {};
 template <> struct FftCfg<80> : FftPlan<80, 20, 2, 20, 4> {};
@@ -350,7 +352,7 @@ template <> struct FftCfg<112> : FftPlan<112, 28, 2, 28, 4> {};
 template <> struct FftCfg<224> : FftPlan<224, 28, 3, 4, 4, 14> {};
 
 // Plans for the fused spectrum pass, whose registers also hold the spectrum row:
-// fewer values per thread where that matters (n = 256: 8 values, radices 8, 8, 4,
+// other stage orders or fewer values per thread where that matters (n = 256: 8 values, radices 8, 8, 4,
 // a 32-thread transform, one LDS pad slot per 8 elements).
 template <int N> struct FftCfgFused : FftCfg<N> {};
 template <> struct FftCfgFused<48> : FftPlan<48, 12, 2, 4, 12> {};

@@ -961,7 +961,7 @@ gs_status plan_autotune(gs_plan_s* p) {
         else p->hint_bits = keep;
     }
     for (int m : {1, 4}) {
-        if (st != GS_OK || !p->cube || !gs_fused_persistent(p->d, p->nf)) break;   // grid fixed by the group count
+        if (st != GS_OK || !p->cube || !gs_fused_persistent(p->d, p->nf, p->kernel == GS_DIPOLAR_3D)) break;   // grid fixed by the group count
         const int keep = p->fused_mult;
         p->fused_mult = m;
         double ms = 0;

@@ -137,9 +137,11 @@ template <int N, int PX> constexpr int line_tiles() {
 // contiguous eighth of the row, so that a die's accesses to X1 and X2 are runs of 1 KB and more
 // instead of every eighth 128-byte line (`part` tiles, the ones that share lines, at least).
 // Measured x passes and y passes together, plain order -> this: 320^3 1652 -> 1616, 384^3 2847 ->
-// 2777, 512^3 6160 -> 5879 us; at 128^3 to 256^3 the same time within 1 %, in 2D (2048^2) 2.5 % slower.
+// 2777, 512^3 6160 -> 5879 us; at 128^3 to 192^3 the same time within 1 %, in 2D (2048^2) 2.5 % slower.
+// At 256 two tiles a run: 615.7 -> 611.5 us.
 template <int N> constexpr int die_run(int tiles, int part) {
-    return N >= 320 && tiles / 8 > part ? tiles / 8 : part;
+    constexpr int least = N == 256 ? 2 : 1;
+    return N >= 320 && tiles / 8 > part ? tiles / 8 : part > least ? part : least;
 }
 
 // Extents of a grid whose axes have their own n (x, y, z; 2D: z = 1).  A pass compiled with
@@ -1095,16 +1097,24 @@ __device__ __forceinline__ void fused_group(gp<cpx> __restrict__ X, gp<const dou
     }
 }
 
+// Waves per SIMD the fused kernels are compiled for.  With 20 values per thread the compiler's own
+// allocation ends a few registers above 256 (n = 160: 258; n = 320: 250, with the energy 258, dipolar
+// 264), which leaves one wave per SIMD; capped at two it spills 2 to 14 registers and runs faster.
+// Evaluations, uncapped -> capped: 160^3 212-215 -> 201-202 (energy 216 -> 212), 320^3 dipolar 1828 ->
+// 1737, energy 1845 -> 1670 us; dipolar 160^3 213-216 -> 227 and 112^3 103 -> 128 (40 spilled) stay uncapped.
+template <int N, int MODE> constexpr int fused_waves() { return N == 320 || (N == 160 && MODE == SPEC_PLAIN) ? 2 : 1; }
+
 // EN: also the energy sum of every pencil into part (fused_energy_store); RV: radix plan.
 template <int N, int DIM, int MODE, int NT = NT_P3, int PZ = Geo<N>::PPZ, bool EN = false, int RV = 0>
-__global__ void __launch_bounds__((PZ * 2 * GeoZ<N, RV>::GZ)) k_fused(cpx* __restrict__ Xg, const double* __restrict__ specg,
+__global__ void __launch_bounds__((PZ * 2 * GeoZ<N, RV>::GZ)) __attribute__((amdgpu_waves_per_eu(fused_waves<N, MODE>())))
+k_fused(cpx* __restrict__ Xg, const double* __restrict__ specg,
                                                               const cpx* __restrict__ twg, int npencils, int kx0,
                                                               DipoleArgs dip, double* __restrict__ part = nullptr) {
     __shared__ cpx lds[PZ * 2 * GeoZ<N, RV>::AZ];
     const int ngroups = (fused_slots<N, DIM, RV>(npencils) + PZ - 1) / PZ;
     // one pencil per block: the +ky and -ky pencils, which read the same spectrum row, on one die
     constexpr int PAIR = DIM == 3 && PZ == 1 ? 2 : 1;
-    if constexpr (!gs_fused_persistent(DIM, N)) {
+    if constexpr (!gs_fused_persistent(DIM, N, MODE == SPEC_DIPOLAR)) {
         // one pencil group per block (the grid must cover all groups).  Without the
         // persistent loop the compiler does not keep the stage twiddles of every thread
         // live across groups: at n = 2048 in 2D, 250 VGPRs instead of 256 + 154 accumulator
@@ -1301,7 +1311,8 @@ __global__ void __launch_bounds__(Geo<N>::TY) k_y_inv_g(const cpx* __restrict__ 
 }
 
 template <int N, int DIM, int MODE, int NT, bool EN = false, bool FT = false>
-__global__ void __launch_bounds__(Geo<N>::TZ) k_fused_g(cpx* __restrict__ Xg, const double* __restrict__ specg,
+__global__ void __launch_bounds__(Geo<N>::TZ) __attribute__((amdgpu_waves_per_eu(fused_waves<N, MODE>())))
+k_fused_g(cpx* __restrict__ Xg, const double* __restrict__ specg,
                                                         const cpx* __restrict__ twg, int npencils, int kx0,
                                                         DipoleArgs dip, Ext ext, double* __restrict__ part = nullptr) {
     __shared__ cpx lds[Geo<N>::PPZ * 2 * Geo<N>::AZ];
@@ -1312,7 +1323,7 @@ __global__ void __launch_bounds__(Geo<N>::TZ) k_fused_g(cpx* __restrict__ Xg, co
             (gp<cpx>)Xg, (gp<const double>)specg, (gp<const cpx>)twg, npencils, kx0, dip, die_tile<PAIR>(g, ngroups),
             threadIdx.x, true, lds, ext, (gp<double>)part);
     };
-    if constexpr (gs_fused_persistent_g(DIM, N)) {
+    if constexpr (gs_fused_persistent_g(DIM, N, MODE == SPEC_DIPOLAR)) {
         for (int g = blockIdx.x; g < ngroups; g += gridDim.x) group(g);
     } else {
         if ((int)blockIdx.x < ngroups) group(blockIdx.x);

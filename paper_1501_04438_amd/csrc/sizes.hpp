@@ -8,16 +8,19 @@
 
 // Grid of the fused pass: persistent (rounds of co-resident blocks looping over pencil
 // groups, the per-thread stage twiddles kept in registers across groups) for 3D cubic grids of
-// n = 256, 384, 512, 640 and 768; one block per pencil group elsewhere, where the twiddles held across
+// n = 256 and, without the dipolar factor (whose registers on top cost occupancy), 384, 512, 640 and
+// 768; one block per pencil group elsewhere, where the twiddles held across
 // groups cost occupancy.  Whole evaluations, one block per group -> persistent: 256^3 651 ->
 // 620, 384^3 2766 -> 2665, 512^3 5874 -> 5809 us, 640^3 16.4 -> 15.5, 768^3 25.6 -> 25.4 ms, but 160^3 200 -> 203, 320^3 1610 ->
-// 1682, dipolar 128^3 87.2 -> 88.6 us, 1024^3 57.2 -> 58.2 ms; 96^3, 128^3 and 192^3 equal.
-constexpr bool gs_fused_persistent(int d, int n) { return d == 3 && (n == 256 || n == 384 || n == 512 || n == 640 || n == 768); }
+// 1682, dipolar 384^3 2693 -> 2910, dipolar 128^3 87.2 -> 88.6 us, 1024^3 57.2 -> 58.2 ms; 96^3, 128^3 and 192^3 equal.
+constexpr bool gs_fused_persistent(int d, int n, bool dipolar) {
+    return d == 3 && (n == 256 || ((n == 384 || n == 512 || n == 640 || n == 768) && !dipolar));
+}
 // The same on grids whose axes differ, by the length of the fused axis: 128x256x512 (z first) 648
 // -> 634, 512x256x128 688 -> 656, 192x256x224 463 -> 450, 96x160x128 equal, but 224x320x192 (28
 // values per thread) 658 -> 759 us.
-constexpr bool gs_fused_persistent_g(int d, int n) {
-    return d == 3 && (n == 128 || n == 192 || n == 256 || n == 384 || n == 512);
+constexpr bool gs_fused_persistent_g(int d, int n, bool dipolar) {
+    return d == 3 && (n == 128 || n == 192 || n == 256 || ((n == 384 || n == 512) && !dipolar));
 }
 
 // Lengths for which the cubic passes are also compiled in tile-shape variants (more or fewer
