@@ -181,7 +181,7 @@ typedef struct {
     double assembly_gflop;   /* 2 Q (n+1)^d, the contraction's algorithmic flops */
     int host_only;
     int slab_planes;         /* kx planes per slab (3D), n+1 in 2D                */
-    int num_steps;           /* kernel launches of one evaluation                 */
+    int num_steps;           /* steps of one evaluation (gs_plan_steps)           */
     int slab_streams;        /* concurrent slab chains (1 = in order)             */
     int x2_planes;           /* kx planes the X2 workspace holds                  */
     int tuned;               /* 1 if the launch variants came from the autotuner  */
@@ -260,8 +260,9 @@ gs_status gs_plan_set_stream(gs_plan p, void* stream);
 /*
  * Evaluation (Algorithm 1, "Actual computation"): u = I1 + A0 rho + c2 Lap rho
  * as one pruned, zero-padded FFT convolution with the stored spectrum, five
- * kernel launches in 3D (x-R2C, y-forward, fused z forward * spectrum *
- * inverse, y-inverse, x-C2R) and three in 2D.  rho and u are device arrays of
+ * passes in 3D (x-R2C, y-forward, fused z forward * spectrum * inverse,
+ * y-inverse, x-C2R) and three in 2D, one launch each; cubic 3D grids of up to
+ * 64 points per axis run the middle three in one launch (same bits).  rho and u are device arrays of
  * n^d FP64; u may alias rho.  The padding never touches memory.
  */
 gs_status gs_eval(gs_plan p, const double* rho_dev, double* u_dev);
@@ -455,7 +456,7 @@ gs_status gs_batch_destroy(gs_batch b);
 gs_status gs_eval_batch(int count, const gs_plan* plans,
                         const double* const* rho_dev, double* const* u_dev);
 
-/* One evaluation is a fixed list of kernel launches ("steps"): 3D: x-R2C, then
+/* One evaluation is a fixed list of passes ("steps"): 3D: x-R2C, then
  * per kx slab (y-forward, fused spectrum pass, y-inverse), then x-C2R; 2D:
  * x-R2C, fused pass, x-C2R.  gs_plan_steps writes each step's pass id (1 =
  * x-R2C, 2 = y-forward, 3 = fused, 4 = y-inverse, 5 = x-C2R) into pass_ids
@@ -471,7 +472,8 @@ gs_status gs_eval_step(gs_plan p, const double* rho_dev, double* u_dev, int step
 /* gs_eval with an event recorded on the plan's stream before the first step and after
  * every step (events: count = steps + 1 hipEvent_t handles created by the caller, for
  * timing the passes of a whole evaluation launched back to back; a NULL entry records
- * nothing at that point).  Errors: INVALID_ARG (count, plan), HIP. */
+ * nothing at that point).  Runs the steps one by one, also where gs_eval joins the
+ * middle ones.  Errors: INVALID_ARG (count, plan), HIP. */
 gs_status gs_eval_events(gs_plan p, const double* rho_dev, double* u_dev, void* const* events, int count);
 
 /* Copies a plan buffer between the device and host memory, for testing the
