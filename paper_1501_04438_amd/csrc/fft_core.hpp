@@ -66,8 +66,8 @@ template <bool INV> __device__ __forceinline__ cpx mul_mi(cpx a) {
 
 // ---------------------------------------------------------------------------
 // Unit roots exp(-2 pi i e / R), correctly rounded, for R dividing 96 (radices
-// 2,3,4,6,8,12,16 and the padding twists of 16, 24, 32 and 48 points), 40 (radices 5
-// and 10, the twists of 20 points) or 56 (radices 7 and 14, the twists of 28 points).
+// 2,3,4,6,8,12,16,24 and the padding twists of 16, 24, 32 and 48 points), 40 (radices 5,
+// 10 and 20, the twists of 20 points) or 56 (radices 7, 14 and 28, the twists of 28 points).
 // ---------------------------------------------------------------------------
 struct CS { double c, s; };
 
