@@ -86,8 +86,8 @@ void free_device(gs_plan_s* p) {
         bool shared = p->twk[i] == p->tw;
         for (int j = 0; j < i; ++j) shared = shared || p->twk[j] == p->twk[i];
         if (p->twk[i] && !shared) (void)hipFree(p->twk[i]);
-        p->twk[i] = nullptr;
     }
+    for (int i = 0; i < 3; ++i) p->twk[i] = nullptr;
     if (p->epart) (void)hipFree(p->epart);
     if (p->mixpart) (void)hipFree(p->mixpart);
     if (p->E) (void)hipFree(p->E);
