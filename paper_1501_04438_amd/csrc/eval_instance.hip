@@ -444,40 +444,48 @@ static hipError_t launch_y_g(const EvalArgs& a, hipStream_t s, int pass, const E
     return hipGetLastError();
 }
 
-template <int N, int DIM, bool FT>
-static hipError_t launch_fused_g(const EvalArgs& a, hipStream_t s, const Ext& ext, const DipoleArgs& dip) {
+template <int N, int DIM, int MODE, bool FT, bool LOOP>
+static hipError_t launch_fused_g_v(const EvalArgs& a, hipStream_t s, const Ext& ext, const DipoleArgs& dip, int np) {
     using Gm = Geo<N>;
     cpx* const X = reinterpret_cast<cpx*>(DIM == 3 ? a.X2 : a.X1);
     const cpx* const tw = reinterpret_cast<const cpx*>(DIM == 3 ? a.twz : a.twy);
     const bool hint = (a.hint_bits >> 2) & 1;
-    const int np = DIM == 3 ? a.kxn * 2 * ext.ny : ext.nx + 1, kx0 = DIM == 3 ? a.kx0 : 0;
+    const int kx0 = DIM == 3 ? a.kx0 : 0;
     const int groups = (fused_slots<N, DIM>(np) + Gm::PPZ - 1) / Gm::PPZ;
     unsigned nb = (unsigned)groups;
-    if (gs_fused_persistent_g(DIM, N, a.dipolar)) {
-        static const int cap = resident_blocks((const void*)k_fused_g<N, DIM, SPEC_PLAIN, 0, false, FT>, Gm::TZ);
+    if constexpr (LOOP) {
+        static const int cap = resident_blocks((const void*)k_fused_g<N, DIM, SPEC_PLAIN, 0, false, FT, true>, Gm::TZ);
         nb = fused_grid(groups, cap, a.fused_grid_mult);
     }
-    double* const ep = a.epart;
-    if constexpr (DIM == 3) {
-        if (a.dipolar) {
-            if (a.energy) {
-                if (hint) k_fused_g<N, 3, SPEC_DIPOLAR, NT_P3, true, FT><<<nb, Gm::TZ, 0, s>>>(X, a.spec, tw, np, kx0, dip, ext, ep);
-                else k_fused_g<N, 3, SPEC_DIPOLAR, 0, true, FT><<<nb, Gm::TZ, 0, s>>>(X, a.spec, tw, np, kx0, dip, ext, ep);
-            } else {
-                if (hint) k_fused_g<N, 3, SPEC_DIPOLAR, NT_P3, false, FT><<<nb, Gm::TZ, 0, s>>>(X, a.spec, tw, np, kx0, dip, ext);
-                else k_fused_g<N, 3, SPEC_DIPOLAR, 0, false, FT><<<nb, Gm::TZ, 0, s>>>(X, a.spec, tw, np, kx0, dip, ext);
-            }
-            return hipGetLastError();
-        }
-    }
     if (a.energy) {
-        if (hint) k_fused_g<N, DIM, SPEC_PLAIN, NT_P3, true, FT><<<nb, Gm::TZ, 0, s>>>(X, a.spec, tw, np, kx0, dip, ext, ep);
-        else k_fused_g<N, DIM, SPEC_PLAIN, 0, true, FT><<<nb, Gm::TZ, 0, s>>>(X, a.spec, tw, np, kx0, dip, ext, ep);
+        if (hint) k_fused_g<N, DIM, MODE, NT_P3, true, FT, LOOP><<<nb, Gm::TZ, 0, s>>>(X, a.spec, tw, np, kx0, dip, ext, a.epart);
+        else k_fused_g<N, DIM, MODE, 0, true, FT, LOOP><<<nb, Gm::TZ, 0, s>>>(X, a.spec, tw, np, kx0, dip, ext, a.epart);
     } else {
-        if (hint) k_fused_g<N, DIM, SPEC_PLAIN, NT_P3, false, FT><<<nb, Gm::TZ, 0, s>>>(X, a.spec, tw, np, kx0, dip, ext);
-        else k_fused_g<N, DIM, SPEC_PLAIN, 0, false, FT><<<nb, Gm::TZ, 0, s>>>(X, a.spec, tw, np, kx0, dip, ext);
+        if (hint) k_fused_g<N, DIM, MODE, NT_P3, false, FT, LOOP><<<nb, Gm::TZ, 0, s>>>(X, a.spec, tw, np, kx0, dip, ext);
+        else k_fused_g<N, DIM, MODE, 0, false, FT, LOOP><<<nb, Gm::TZ, 0, s>>>(X, a.spec, tw, np, kx0, dip, ext);
     }
     return hipGetLastError();
+}
+
+template <int N, int DIM, int MODE, bool FT>
+static hipError_t launch_fused_g_mode(const EvalArgs& a, hipStream_t s, const Ext& ext, const DipoleArgs& dip) {
+    const int np = DIM == 3 ? a.kxn * 2 * ext.ny : ext.nx + 1;
+    constexpr bool DIPOLAR = MODE == SPEC_DIPOLAR;
+    constexpr Loop R = gs_fused_loop_g(DIM, N, DIPOLAR);
+    if constexpr (R != Loop::never) {
+        if (gs_fused_persistent_g(DIM, N, DIPOLAR, a.energy != nullptr, 16.0 * np * N))
+            return launch_fused_g_v<N, DIM, MODE, FT, true>(a, s, ext, dip, np);
+    }
+    if constexpr (R != Loop::always) return launch_fused_g_v<N, DIM, MODE, FT, false>(a, s, ext, dip, np);
+    return hipErrorInvalidValue;      // not reached
+}
+
+template <int N, int DIM, bool FT>
+static hipError_t launch_fused_g(const EvalArgs& a, hipStream_t s, const Ext& ext, const DipoleArgs& dip) {
+    if constexpr (DIM == 3) {
+        if (a.dipolar) return launch_fused_g_mode<N, DIM, SPEC_DIPOLAR, FT>(a, s, ext, dip);
+    }
+    return launch_fused_g_mode<N, DIM, SPEC_PLAIN, FT>(a, s, ext, dip);
 }
 
 // Pass `pass` of a grid whose axes have their own n, N being the length the pass transforms

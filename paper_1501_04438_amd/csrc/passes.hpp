@@ -1310,7 +1310,8 @@ __global__ void __launch_bounds__(Geo<N>::TY) k_y_inv_g(const cpx* __restrict__ 
                                                  blockIdx.y, threadIdx.x, true, lds, ext);
 }
 
-template <int N, int DIM, int MODE, int NT, bool EN = false, bool FT = false>
+// LOOP: the grid is persistent (gs_fused_persistent_g).
+template <int N, int DIM, int MODE, int NT, bool EN, bool FT, bool LOOP>
 __global__ void __launch_bounds__(Geo<N>::TZ) __attribute__((amdgpu_waves_per_eu(fused_waves<N, MODE>())))
 k_fused_g(cpx* __restrict__ Xg, const double* __restrict__ specg,
                                                         const cpx* __restrict__ twg, int npencils, int kx0,
@@ -1323,7 +1324,7 @@ k_fused_g(cpx* __restrict__ Xg, const double* __restrict__ specg,
             (gp<cpx>)Xg, (gp<const double>)specg, (gp<const cpx>)twg, npencils, kx0, dip, die_tile<PAIR>(g, ngroups),
             threadIdx.x, true, lds, ext, (gp<double>)part);
     };
-    if constexpr (gs_fused_persistent_g(DIM, N, MODE == SPEC_DIPOLAR)) {
+    if constexpr (LOOP) {
         for (int g = blockIdx.x; g < ngroups; g += gridDim.x) group(g);
     } else {
         if ((int)blockIdx.x < ngroups) group(blockIdx.x);

@@ -16,11 +16,30 @@
 constexpr bool gs_fused_persistent(int d, int n, bool dipolar) {
     return d == 3 && (n == 256 || ((n == 384 || n == 512 || n == 640 || n == 768) && !dipolar));
 }
-// The same on grids whose axes differ, by the length of the fused axis: 128x256x512 (z first) 648
-// -> 634, 512x256x128 688 -> 656, 192x256x224 463 -> 450, 96x160x128 equal, but 224x320x192 (28
-// values per thread) 658 -> 759 us.
-constexpr bool gs_fused_persistent_g(int d, int n, bool dipolar) {
-    return d == 3 && (n == 128 || n == 192 || n == 256 || ((n == 384 || n == 512) && !dipolar));
+// The same on grids whose axes differ, by the length n of the fused axis: always, never, or where
+// the pass's array X2 (a slab's planes) is larger than the 256 MB cache (with the energy's sums,
+// whose kernel has two waves either way, from 190 MB).  Whole evaluations (z
+// first), one block per group -> persistent:
+//   plain: 128x256x512 648 -> 634, 512x256x128 698 -> 661, 384x256x320 1570 -> 1470, 256x192x320 637
+//   -> 612, 128x256x192 243 -> 238; 192x128x160 156 -> 158 (energy 170 -> 166); but 224x320x192 (28
+//   values per thread) 658 -> 759 us
+//   dipolar, 192 and 256: 192x128x160 164 -> 159, 192x256x128 261 -> 250, 256x128x192 257 -> 251,
+//   256x192x320 668 -> 630, 256x256x512 1513 -> 1430 us; 384 and 512 equal
+//   dipolar, 128: the loop takes the kernel from four waves per SIMD to two, which costs as long as
+//   the cache serves it: 128x96x96 (X2 38 MB) 60.3 -> 62.3, 128x96x160 85.1 -> 89.4, 128x256x192
+//   (202 MB) 247.5 -> 252.8, 128x256x224 (236 MB) 312 -> 317, and gains beyond: 128x256x320 (336 MB)
+//   421 -> 420, 128x384x256 506 -> 492, 128x512x256 670 -> 655; with the energy 128x160x256 (168 MB)
+//   230.8 -> 233.6, 128x256x192 (202 MB) 272.3 -> 269.6, 128x256x224 340 -> 333, 128x256x320 459 ->
+//   442 us.
+enum class Loop { never, always, beyond_cache };
+constexpr Loop gs_fused_loop_g(int d, int n, bool dipolar) {
+    if (d != 3) return Loop::never;
+    if (n == 128) return dipolar ? Loop::beyond_cache : Loop::always;
+    return n == 192 || n == 256 || ((n == 384 || n == 512) && !dipolar) ? Loop::always : Loop::never;
+}
+constexpr bool gs_fused_persistent_g(int d, int n, bool dipolar, bool energy, double x2_bytes) {
+    const Loop r = gs_fused_loop_g(d, n, dipolar);
+    return r == Loop::always || (r == Loop::beyond_cache && x2_bytes > (energy ? 190e6 : 256e6));
 }
 
 // Lengths for which the cubic passes are also compiled in tile-shape variants (more or fewer

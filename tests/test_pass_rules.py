@@ -1,0 +1,40 @@
+"""The rules that choose a pass's form, read from the compiled sources by a host program."""
+
+import os
+import shutil
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    cc = next((c for c in (os.environ.get("HIPCC"), "/opt/rocm/bin/hipcc", shutil.which("hipcc")) if c and os.path.exists(c)), None)
+    if cc is None:
+        pytest.skip("hipcc not available")
+    exe = str(tmp_path_factory.mktemp("rules") / "pass_rules_driver")
+    r = subprocess.run([cc, "-x", "hip", "--cuda-host-only", "--offload-arch=gfx950", "-std=c++20", "-O1",
+                        "-Wno-unused-command-line-argument", os.path.join(HERE, "native", "pass_rules_driver.cpp"),
+                        "-o", exe], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stderr
+    return [line.split() for line in r.stdout.splitlines()]
+
+
+def test_fused_loop_of_unequal_axes(rules):
+    """The persistent loop of the fused pass where it was measured to gain: at 128 the dipolar
+    kernel loses two of its four waves per SIMD to it, so there it starts beyond the cache."""
+    loop = {int(n): (p, d) for tag, n, p, d in (r for r in rules if r[0] == "loop_g")}
+    assert loop[128] == ("always", "beyond_cache")
+    assert loop[192] == loop[256] == ("always", "always")
+    assert loop[384] == loop[512] == ("always", "never")
+    assert all(v == ("never", "never") for n, v in loop.items() if n not in (128, 192, 256, 384, 512))
+    at = {(int(r[1]), int(r[2]), r[3] == "1"): (r[4] == "1", r[5] == "1") for r in rules if r[0] == "persistent_g"}
+    for mb, ev, en in ((38, False, False), (168, False, False), (202, False, True), (236, False, True), (269, True, True),
+                       (538, True, True)):
+        assert at[128, mb, False] == (True, ev) and at[128, mb, True] == (True, en)
+    assert at[192, 38, False] == (True, True) and at[512, 538, False] == (True, False)
+    assert at[224, 538, True] == (False, False)
