@@ -376,6 +376,7 @@ int GS_CAT(tile_variants_, GS_N)() {
 template <int PX, int PF, int PI>
 static hipError_t launch_x_g(const EvalArgs& a, hipStream_t s, int pass, const Ext& ext) {
     constexpr int N = GS_N, G = Geo<N>::G, P0 = Geo<N>::PPX;
+    constexpr bool FT5 = p5_unchecked<N>();
     cpx* const X1 = reinterpret_cast<cpx*>(a.X1);
     const cpx* const tw = reinterpret_cast<const cpx*>(a.twx);
     const bool hint = (a.hint_bits >> (pass - 1)) & 1;
@@ -401,11 +402,11 @@ static hipError_t launch_x_g(const EvalArgs& a, hipStream_t s, int pass, const E
             }
         } else {
             if (sc) {
-                if (hint) k_x_c2r_g<N, NT_P5, true, P0, true><<<grid(P0), P0 * G, 0, s>>>(X1, a.u, tw, ext, a.oscale);
-                else k_x_c2r_g<N, 0, true, P0, true><<<grid(P0), P0 * G, 0, s>>>(X1, a.u, tw, ext, a.oscale);
+                if (hint) k_x_c2r_g<N, NT_P5, true, P0, FT5><<<grid(P0), P0 * G, 0, s>>>(X1, a.u, tw, ext, a.oscale);
+                else k_x_c2r_g<N, 0, true, P0, FT5><<<grid(P0), P0 * G, 0, s>>>(X1, a.u, tw, ext, a.oscale);
             } else {
-                if (hint) k_x_c2r_g<N, NT_P5, false, P0, true><<<grid(P0), P0 * G, 0, s>>>(X1, a.u, tw, ext, 1.0);
-                else k_x_c2r_g<N, 0, false, P0, true><<<grid(P0), P0 * G, 0, s>>>(X1, a.u, tw, ext, 1.0);
+                if (hint) k_x_c2r_g<N, NT_P5, false, P0, FT5><<<grid(P0), P0 * G, 0, s>>>(X1, a.u, tw, ext, 1.0);
+                else k_x_c2r_g<N, 0, false, P0, FT5><<<grid(P0), P0 * G, 0, s>>>(X1, a.u, tw, ext, 1.0);
             }
         }
         return hipGetLastError();

@@ -458,6 +458,14 @@ template <int N, int PX, int XV = 0> constexpr int p5_threads() {
     return (p5_split<N, PX, XV>() ? 2 : 1) * PX * GeoX<N, XV>::G;
 }
 
+// Whether the two-phase tile (x_c2r_tile) of a grid whose axes differ runs unchecked where the rows
+// fill its tiles.  At 24 values per thread (n = 1536) it does not: the 48 loads of a half and the
+// sums kept from the first leave no free register, and without the check's branch around them the
+// compiler moves every pair of loads down to its use and waits for it.  Unchecked -> checked: 2D
+// 48x1536 35.2 -> 28.9, 512x1536 49.4 -> 44.4, 1024x1536 59.3 -> 55.8 us; at 20 values and fewer
+// unchecked: 48x2048 28.6 (checked 29.4), 64x64x12 17.3 (19.1) us.
+template <int N> constexpr bool p5_unchecked() { return Geo<N>::E < 24 || p5_split_len<N>(); }
+
 // HV: X1 holds the two halves k_plane leaves (the second one (N + 1) N N values on), whose sum
 // is the transform's input.
 // RECT: as in x_r2c_tile_split.

@@ -9,6 +9,7 @@ using namespace gsk;
 template <int N> static void rules() {
     const char* loop[] = {"never", "always", "beyond_cache"};
     std::printf("loop_g %d %s %s\n", N, loop[(int)gs_fused_loop_g(3, N, false)], loop[(int)gs_fused_loop_g(3, N, true)]);
+    std::printf("p5_unchecked %d %d %d\n", N, (int)p5_split_len<N>(), (int)p5_unchecked<N>());
     for (double mb : {38.0, 168.0, 202.0, 236.0, 269.0, 336.0, 538.0})
         for (int e = 0; e < 2; ++e)
             std::printf("persistent_g %d %.0f %d %d %d\n", N, mb, e, (int)gs_fused_persistent_g(3, N, false, e, mb * 1e6),

@@ -38,3 +38,11 @@ def test_fused_loop_of_unequal_axes(rules):
         assert at[128, mb, False] == (True, ev) and at[128, mb, True] == (True, en)
     assert at[192, 38, False] == (True, True) and at[512, 538, False] == (True, False)
     assert at[224, 538, True] == (False, False)
+
+
+def test_two_phase_inverse_at_24_values_is_checked(rules):
+    """The two-phase x-inverse tile holds 24 values per thread at 1536 only; its unchecked form
+    waits for every pair of loads there."""
+    got = {int(r[1]): (r[2] == "1", r[3] == "1") for r in rules if r[0] == "p5_unchecked"}
+    assert got[1536] == (False, False)
+    assert all(unchecked for n, (_, unchecked) in got.items() if n != 1536)
