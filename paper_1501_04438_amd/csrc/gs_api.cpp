@@ -194,10 +194,14 @@ size_t workspace_cap() {
 // -> 42.5, 112^3 107.9 -> 104.8, 128^3 92.7 -> 88.1, 160^3 (131 MB) 218.6 -> 205.8 us; 192^3
 // (226 MB) equal, 224^3 (370 MB) 611 with all against 624; 2D 1024^2 41.2 -> 39.7, 2048^2 106.6 ->
 // 102.8 us.
-int default_hints(int d, const int nk[3]) {
+// Plans split into kx slabs (slab planes each) rewrite a slab's part of X2 before the next: up to
+// 20 MB of it, all hints again (P2 stored through, 128^3: slabs of 15 planes 219 -> 199, 26 planes
+// (14 MB) 155.1 -> 148.8, 96^3: 20 planes 117.7 -> 115.7 us); 43 planes (23 MB) equal, 160^3 with 54
+// planes (44 MB) 243 with all against 236.
+int default_hints(int d, const int nk[3], int slab) {
     if (d == 2) return 24;
-    const double x2 = 32.0 * (nk[0] + 1.0) * nk[1] * nk[2];
-    return x2 <= 20e6 ? 0 : x2 <= 160e6 ? 24 : 27;
+    const double plane = 32.0 * nk[1] * nk[2], x2 = plane * (nk[0] + 1.0);
+    return x2 <= 20e6 ? 0 : x2 <= 160e6 && plane * slab > 20e6 ? 24 : 27;
 }
 
 gs_status plan_autotune(gs_plan_s* p);
@@ -557,7 +561,6 @@ gs_status gs_plan_create(gs_plan* out, gs_kernel k, int d, const int64_t* n, con
     p->flags = opt.flags;
     p->host_only = host_only;
     p->tile_bits = opt.tile_variants & 8191;
-    p->hint_bits = opt.launch_hints > 0 ? (opt.launch_hints - 1) & 31 : default_hints(d, nk);
     p->stream = (hipStream_t)opt.stream;
     for (int i = 0; i < 3; ++i) {
         p->dn[i] = opt.dipole_n[i];
@@ -612,6 +615,7 @@ gs_status gs_plan_create(gs_plan* out, gs_kernel k, int d, const int64_t* n, con
         p->slab = (int)n1;
         p->steps = {{1, 0}, {3, 0}, {5, 0}};
     }
+    p->hint_bits = opt.launch_hints > 0 ? (opt.launch_hints - 1) & 31 : default_hints(d, nk, p->slab);
     // twiddle tables: one of length n for a cube, else one per distinct axis length
     size_t tw_bytes = 0;
     for (int i = 0; i < d; ++i) {
