@@ -9,6 +9,7 @@ paper_1501_04438_amd.build` or call build().
 from __future__ import annotations
 
 import concurrent.futures as cf
+import hashlib
 import os
 import re
 import shutil
@@ -40,6 +41,17 @@ def sizes() -> list[int]:
     return [int(v) for v in re.findall(r"X\((\d+)\)", m.group(1))]
 
 
+def source_id() -> str:
+    """Digest of the sources and flags: part of the autotuner's cache keys, so that a choice timed on
+    other kernels is not taken over."""
+    h = hashlib.sha256(" ".join(FLAGS).encode())
+    for f in sorted(f for f in os.listdir(CSRC) if f.endswith((".cpp", ".hpp", ".hip"))):
+        h.update(f.encode())
+        with open(os.path.join(CSRC, f), "rb") as fp:
+            h.update(fp.read())
+    return h.hexdigest()[:12]
+
+
 def _run(cmd):
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
@@ -62,7 +74,8 @@ def build(jobs: int | None = None, verbose: bool = False) -> str:
     # The mixture gradient's contraction (mixture.hip) is built the same way: 132 VGPRs and no
     # accumulator copies instead of 164 registers and 64 copies per tile.
     extra = {"device_dispatch.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
-             "mixture.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
+             "mixture.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
+             "autotune.cpp": [f'-DGS_SOURCE_ID="{source_id()}"']}
     for src in ("device_dispatch.hip", "batch.hip", "host_plan.cpp", "gs_api.cpp", "batch_api.cpp",
                 "autotune.cpp", "static_eval.hip", "mixture.hip"):
         units.append([cc, *FLAGS, *extra.get(src, []), "-c", os.path.join(CSRC, src),

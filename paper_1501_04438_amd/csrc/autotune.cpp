@@ -10,6 +10,10 @@
 #include <mutex>
 #include <sstream>
 
+#ifndef GS_SOURCE_ID
+#error "GS_SOURCE_ID (digest of the sources, from the build script) must be defined"
+#endif
+
 namespace gsapi {
 
 namespace {
@@ -80,7 +84,7 @@ std::string tune_device_key(int device) {
     std::string arch = prop.gcnArchName;
     const size_t colon = arch.find(':');
     if (colon != std::string::npos) arch.resize(colon);
-    return arch + "/cu" + std::to_string(prop.multiProcessorCount);
+    return arch + "/cu" + std::to_string(prop.multiProcessorCount) + "/src" GS_SOURCE_ID;
 }
 
 bool tune_lookup(const std::string& key, TuneEntry& e) {

@@ -1,0 +1,56 @@
+"""What the autotuners keep: choices timed on other kernels are not taken over."""
+
+import json
+import re
+
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import paper_1501_04438_amd as gs
+
+
+def need_gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+def other_builds(path, out, digest):
+    """The entries of a cache file as another build would have left them."""
+    entries = {re.sub(r"/src[0-9a-f]+", digest, k): v for k, v in json.loads(path.read_text()).items()}
+    lines = ['  "%s": {"schedule": %d, "tiles_per_task": %d, "largest_first": %d, "grid": %d, "ms": %g}'
+             % (k, v["schedule"], v["tiles_per_task"], v["largest_first"], v["grid"], v["ms"]) for k, v in entries.items()]
+    out.write_text("{\n" + ",\n".join(lines) + "\n}\n")
+    return entries
+
+
+# "": a file of a build whose keys held no digest
+@pytest.mark.gpu
+@pytest.mark.parametrize("digest", ["", "/src0123456789ab"])
+def test_plan_choice_of_other_kernels_is_timed_again(digest, tmp_path, monkeypatch):
+    need_gpu()
+    new, old = tmp_path / "new.json", tmp_path / "old.json"
+    monkeypatch.setenv("GS_AUTOTUNE_CACHE", str(new))
+    gs.Plan("coulomb3d", n=24, L=5.0, autotune=True)
+    kept = other_builds(new, old, digest)
+    monkeypatch.setenv("GS_AUTOTUNE_CACHE", str(old))
+    plan = gs.Plan("coulomb3d", n=24, L=5.0, autotune=True)
+    assert plan.info["tune_candidates"] > 0
+    # the other build's entry stays in the file, beside the new one
+    entries = json.loads(old.read_text())
+    assert set(kept) < set(entries) and len(entries) == 2
+
+
+@pytest.mark.gpu
+def test_batch_choice_of_other_kernels_is_timed_again(tmp_path, monkeypatch):
+    need_gpu()
+    new, old = tmp_path / "new.json", tmp_path / "old.json"
+    monkeypatch.setenv("GS_AUTOTUNE_CACHE", str(new))
+    plans = [gs.Plan("coulomb3d", n=16, L=5.0) for _ in range(4)]
+    x = [torch.ones((16,) * 3, dtype=torch.float64, device="cuda:0") for _ in plans]
+    gs.Batch(plans, schedule="auto").eval(x)
+    other_builds(new, old, "")
+    monkeypatch.setenv("GS_AUTOTUNE_CACHE", str(old))
+    b = gs.Batch(plans, schedule="auto")
+    b.eval(x)
+    assert b.info["candidates"] > 0
