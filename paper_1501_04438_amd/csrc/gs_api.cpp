@@ -301,12 +301,17 @@ static hipError_t run_step(gs_plan p, gsk::EvalArgs& a, int step, hipStream_t s)
     return e;
 }
 
-// A whole evaluation on stream s, in order.  Small cubic 3D grids run the three middle steps as
-// one launch per evaluation (gsk::PASS_PLANE; the same bits) when X2 holds every plane.
+// Whether a whole evaluation runs its three middle steps as one launch (gsk::PASS_PLANE; the same
+// bits): small cubic 3D grids whose X2 holds every plane.
+static bool plane_path(const gs_plan_s* p) {
+    return p->d == 3 && p->cube && p->nslabs == 1 && p->x2_planes == p->nk[0] + 1 && gsk::plane_fused(p->nf);
+}
+
+// A whole evaluation on stream s, in order.
 static hipError_t run_steps(gs_plan p, gsk::EvalArgs& a, hipStream_t s) {
     const int last = (int)p->steps.size() - 1;
     hipError_t e = hipSuccess;
-    if (p->d == 3 && p->cube && p->nslabs == 1 && p->x2_planes == p->nk[0] + 1 && gsk::plane_fused(p->nf)) {
+    if (plane_path(p)) {
         e = run_step(p, a, 0, s);
         if (e == hipSuccess) e = gsk::launch_eval(a, s, gsk::PASS_PLANE);
         if (e == hipSuccess) e = gsk::launch_eval(a, s, gsk::PASS_X_INVERSE_HALVES);
@@ -921,8 +926,8 @@ gs_status time_plan(gs_plan_s* p, const double* rho, double* u, double& ms) {
 }
 
 // Greedy search over the launch variants: starting from the compiled defaults, flip each
-// pass's cache-hint variant in turn and keep what is faster, then try one and four rounds of
-// co-resident blocks in the fused pass, then the tile shapes and the radix plans.  None but
+// pass's cache-hint variant in turn (of the passes whose launches take one) and keep what is faster,
+// then try one and four rounds of co-resident blocks in the fused pass, then the tile shapes and the radix plans.  None but
 // the radix plans changes the result (they agree with the default to rounding).  Timed on
 // scratch buffers, so the caller's data is never evaluated by a candidate.
 gs_status plan_autotune(gs_plan_s* p) {
@@ -952,12 +957,16 @@ gs_status plan_autotune(gs_plan_s* p) {
     if (e != hipSuccess) st = hip_fail(e, "autotune scratch");
     double best = 1e300;
     if (st == GS_OK) st = time_plan(p, rho, u, best);
-    const int passes[5] = {1, 2, 3, 4, 5};
-    for (int pass : passes) {
+    // hint bits flipped together in one candidate: one pass at a time; where the middle passes are
+    // one launch, which takes no hints, the x passes alone and both (all their four settings)
+    const std::vector<int> flips = plane_path(p) ? std::vector<int>{1, 16, 17}
+                                   : p->d == 2   ? std::vector<int>{1, 4, 16}
+                                                 : std::vector<int>{1, 2, 4, 8, 16};
+    const int start = p->hint_bits;
+    for (int f : flips) {
         if (st != GS_OK) break;
-        if (p->d == 2 && (pass == 2 || pass == 4)) continue;
         const int keep = p->hint_bits;
-        p->hint_bits ^= 1 << (pass - 1);
+        p->hint_bits = (plane_path(p) ? start : keep) ^ f;
         double ms = 0;
         st = time_plan(p, rho, u, ms);
         p->tune_candidates++;

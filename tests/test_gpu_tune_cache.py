@@ -54,3 +54,17 @@ def test_batch_choice_of_other_kernels_is_timed_again(tmp_path, monkeypatch):
     b = gs.Batch(plans, schedule="auto")
     b.eval(x)
     assert b.info["candidates"] > 0
+
+
+# cubes up to 64^3 run their middle passes in one launch, which takes no hints: the tuner leaves
+# their bits alone (a slab plan runs them one by one and times them)
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,planes", [(16, 0), (48, 0), (64, 0), (64, 33)])
+def test_hints_that_no_launch_takes_are_not_timed(n, planes, tmp_path, monkeypatch):
+    need_gpu()
+    monkeypatch.setenv("GS_AUTOTUNE_CACHE", str(tmp_path / "tune.json"))
+    start = gs.Plan("coulomb3d", n=n, L=5.0, slab_planes=planes).info["hint_bits"]
+    tuned = gs.Plan("coulomb3d", n=n, L=5.0, slab_planes=planes, autotune=True).info
+    assert tuned["tune_candidates"] == (5 if planes else 3)
+    if not planes:
+        assert (tuned["hint_bits"] ^ start) & 14 == 0
