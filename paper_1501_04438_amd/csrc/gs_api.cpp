@@ -925,6 +925,13 @@ gs_status time_plan(gs_plan_s* p, const double* rho, double* u, double& ms) {
     return st;
 }
 
+// Whether the fused pass of whole evaluations runs in rounds of co-resident blocks.
+bool fused_rounds(const gs_plan_s* p) {
+    const bool dipolar = p->kernel == GS_DIPOLAR_3D;
+    if (p->cube) return gs_fused_persistent(p->d, p->nf, dipolar);
+    return p->d == 3 && gs_fused_persistent_g(3, p->nk[2], dipolar, false, 32.0 * p->slab * p->nk[1] * p->nk[2]);
+}
+
 // Greedy search over the launch variants: starting from the compiled defaults, flip each
 // pass's cache-hint variant in turn (of the passes whose launches take one) and keep what is faster,
 // then try one and four rounds of co-resident blocks in the fused pass, then the tile shapes and the radix plans.  None but
@@ -974,7 +981,7 @@ gs_status plan_autotune(gs_plan_s* p) {
         else p->hint_bits = keep;
     }
     for (int m : {1, 4}) {
-        if (st != GS_OK || !p->cube || !gs_fused_persistent(p->d, p->nf, p->kernel == GS_DIPOLAR_3D)) break;   // grid fixed by the group count
+        if (st != GS_OK || !fused_rounds(p)) break;        // grid fixed by the group count
         const int keep = p->fused_mult;
         p->fused_mult = m;
         double ms = 0;

@@ -68,3 +68,18 @@ def test_hints_that_no_launch_takes_are_not_timed(n, planes, tmp_path, monkeypat
     assert tuned["tune_candidates"] == (5 if planes else 3)
     if not planes:
         assert (tuned["hint_bits"] ^ start) & 14 == 0
+
+
+# the rounds of the persistent fused pass are tried where it is persistent, on unequal axes too
+# (fused axis z: 128 plain; dipolar 128 on a grid inside the cache and z = 24 run one block per group)
+@pytest.mark.gpu
+@pytest.mark.parametrize("kernel,shape,rounds", [("coulomb3d", (128, 16, 32), 2), ("dipolar3d", (128, 16, 32), 0),
+                                                 ("dipolar3d", (192, 16, 32), 2), ("coulomb3d", (24, 16, 32), 0)])
+def test_rounds_are_timed_on_unequal_axes(kernel, shape, rounds, tmp_path, monkeypatch):
+    need_gpu()
+    monkeypatch.setenv("GS_AUTOTUNE_CACHE", str(tmp_path / "tune.json"))
+    kw = {"dipole": ((0.6, 0.8, 0.0), (0.0, 0.6, 0.8))} if kernel == "dipolar3d" else {}
+    x = torch.ones(shape, dtype=torch.float64, device="cuda:0")
+    tuned = gs.Plan(kernel, n=shape, L=5.0, autotune=True, **kw)
+    assert tuned.info["tune_candidates"] == 5 + rounds
+    assert torch.equal(tuned.eval(x), gs.Plan(kernel, n=shape, L=5.0, **kw).eval(x))
