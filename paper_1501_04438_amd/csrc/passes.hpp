@@ -120,7 +120,7 @@ template <int N, int XV = 0> struct GeoX {
 // 8 dies in turn) at about the same time, and its L2 merges the parts of a line.  Other grids and
 // remainders keep the plain order.
 template <int LPT>
-__device__ __forceinline__ int die_tile(int b, int nb) {
+__host__ __device__ __forceinline__ int die_tile(int b, int nb) {
     if constexpr (LPT <= 1) return b;
     const int whole = nb / (8 * LPT) * (8 * LPT);
     if (b >= whole) return b;
@@ -243,11 +243,17 @@ __device__ __forceinline__ void x_r2c_tile(gp<const double> __restrict__ rho, gp
     }
 }
 
-// The tile of the calling block of an x pass (3D: one row of tiles per z).
-template <int N, int PX> __device__ __forceinline__ int x_die_tile() {
+// The tile of block b of the nb of a row, in the x passes (several rows of tiles, one per z: 3D) and
+// in the y passes.
+template <int N, int PX> __host__ __device__ __forceinline__ int x_tile_of(int b, int nb, bool rows) {
     constexpr int part = line_tiles<N, PX>(), run = die_run<N>(N / (2 * PX), part);
-    return run > part && gridDim.y > 1 ? die_tile<run>(blockIdx.x, gridDim.x)
-                                       : die_tile<part>(blockIdx.x, gridDim.x);
+    return run > part && rows ? die_tile<run>(b, nb) : die_tile<part>(b, nb);
+}
+template <int N, int PX> __device__ __forceinline__ int x_die_tile() {
+    return x_tile_of<N, PX>(blockIdx.x, gridDim.x, gridDim.y > 1);
+}
+template <int N, int PY> __host__ __device__ __forceinline__ int y_tile_of(int b, int nb) {
+    return die_tile<die_run<N>(N / PY, PY == 8 ? 2 : 1)>(b, nb);
 }
 
 // At n = 2048 the compiler's own allocation takes 256 VGPRs + 42 accumulator registers (one wave
@@ -633,7 +639,7 @@ __global__ void __launch_bounds__((PY * GeoX<N, YV>::G)) k_y_fwd(const cpx* __re
                                                                 const cpx* __restrict__ tw, int kx0) {
     __shared__ cpx lds[PY * Geo<N>::A];
     y_fwd_tile<N, NT, true, PY, YV>((gp<const cpx>)X1, (gp<cpx>)X2, (gp<const cpx>)tw, kx0,
-                                    die_tile<die_run<N>(N / PY, PY == 8 ? 2 : 1)>(blockIdx.x, gridDim.x), blockIdx.y, threadIdx.x, true, lds);
+                                    y_tile_of<N, PY>(blockIdx.x, gridDim.x), blockIdx.y, threadIdx.x, true, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -682,7 +688,7 @@ __global__ void __launch_bounds__((PY * GeoX<N, YV>::G)) k_y_inv(const cpx* __re
                                                                 const cpx* __restrict__ tw, int kx0) {
     __shared__ cpx lds[PY * Geo<N>::A];
     y_inv_tile<N, NT, true, PY, YV>((gp<const cpx>)X2, (gp<cpx>)X1, (gp<const cpx>)tw, kx0,
-                                    die_tile<die_run<N>(N / PY, PY == 8 ? 2 : 1)>(blockIdx.x, gridDim.x), blockIdx.y, threadIdx.x, true, lds);
+                                    y_tile_of<N, PY>(blockIdx.x, gridDim.x), blockIdx.y, threadIdx.x, true, lds);
 }
 
 // P4 of a cubic grid with the two halves of the padded inverse on the two 32-lane halves of every
@@ -726,7 +732,7 @@ __global__ void __launch_bounds__((2 * PY * Geo<N>::G)) k_y_inv_split(const cpx*
                                                                      const cpx* __restrict__ tw, int kx0) {
     __shared__ cpx lds[2 * PY * Geo<N>::A];
     y_inv_tile_split<N, NT, PY>((gp<const cpx>)X2, (gp<cpx>)X1, (gp<const cpx>)tw, kx0,
-                                die_tile<die_run<N>(N / PY, PY == 8 ? 2 : 1)>(blockIdx.x, gridDim.x), blockIdx.y,
+                                y_tile_of<N, PY>(blockIdx.x, gridDim.x), blockIdx.y,
                                 threadIdx.x, lds);
 }
 

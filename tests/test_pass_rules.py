@@ -46,3 +46,16 @@ def test_two_phase_inverse_at_24_values_is_checked(rules):
     got = {int(r[1]): (r[2] == "1", r[3] == "1") for r in rules if r[0] == "p5_unchecked"}
     assert got[1536] == (False, False)
     assert all(unchecked for n, (_, unchecked) in got.items() if n != 1536)
+
+
+def test_block_orders_are_permutations(rules):
+    """The kernels' own block-to-tile orders, at every length, tile and row they are launched with."""
+    got = [r for r in rules if r[0] == "orders"]
+    assert len(got) == 6 * sum(r[0] == "runs" for r in rules) and all(r[3:] == ["1", "1", "1"] for r in got)
+
+
+def test_runs_of_a_die(rules):
+    """From 320 a die works a contiguous eighth of a row of tiles, at 256 two tiles, below only the
+    tiles that share lines."""
+    runs = {int(r[1]): (int(r[2]), int(r[3])) for r in rules if r[0] == "runs"}
+    assert runs[320] == (5, 5) and runs[512] == (8, 8) and runs[256] == (2, 2) and runs[128] == (1, 1)
