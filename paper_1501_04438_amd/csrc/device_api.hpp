@@ -24,7 +24,6 @@ struct EvalArgs {
     double cdiag[3] = {0, 0, 0};
     double ccross[3] = {0, 0, 0};
     double nm_over_M = 0.0;
-    int max_blocks_fused = 0;         // persistent grid size of the 3D fused pass (0 = device fill)
     int kx0 = 0, kxn = 0;             // 3D passes 2-4: the kx slab [kx0, kx0 + kxn); X2 holds the slab
     // Launch variants (none changes a single bit of the result): bit p-1 clear selects
     // plain (cached) memory accesses for pass p instead of its cache-hint default;

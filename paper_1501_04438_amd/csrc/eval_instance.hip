@@ -104,46 +104,28 @@ static hipError_t launch_x_forward_v(const EvalArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
-// P1 with its halves on the lane halves (x_r2c_tile_split), PX row pairs per block; with the
-// density at its own extents where a.emb.  PX = 0: the pass keeps x_r2c_tile.
+// P1 with its halves on the lane halves (x_r2c_tile_split), PX row pairs per block.  PX = 0: the
+// pass keeps x_r2c_tile.
 template <int PX>
 static hipError_t launch_x_forward_split(const EvalArgs& a, hipStream_t s) {
     constexpr int N = GS_N;
-    const cpx* const tw = reinterpret_cast<const cpx*>(a.tw);
-    cpx* const X1 = reinterpret_cast<cpx*>(a.X1);
-    const bool hint = a.hint_bits & 1;
-    Ext ext;
-    ext.nx = a.px;
-    ext.ny = a.py;
-    ext.nz = a.d == 3 ? a.pz : 1;
     if constexpr (PX > 0) {
         constexpr int T = 2 * PX * Geo<N>::G;
+        const cpx* const tw = reinterpret_cast<const cpx*>(a.tw);
+        cpx* const X1 = reinterpret_cast<cpx*>(a.X1);
         const dim3 gx((N + 2 * PX - 1) / (2 * PX), a.d == 3 ? N : 1);
-        if (a.emb) {
-            if (hint) k_x_r2c_emb_split<N, NT_P1, PX><<<gx, T, 0, s>>>(a.rho, X1, tw, ext);
-            else k_x_r2c_emb_split<N, 0, PX><<<gx, T, 0, s>>>(a.rho, X1, tw, ext);
-        } else {
-            if (hint) k_x_r2c_split<N, NT_P1, PX><<<gx, T, 0, s>>>(a.rho, X1, tw);
-            else k_x_r2c_split<N, 0, PX><<<gx, T, 0, s>>>(a.rho, X1, tw);
-        }
+        if (a.hint_bits & 1) k_x_r2c_split<N, NT_P1, PX><<<gx, T, 0, s>>>(a.rho, X1, tw);
+        else k_x_r2c_split<N, 0, PX><<<gx, T, 0, s>>>(a.rho, X1, tw);
+        return hipGetLastError();
     } else {
-        constexpr int P = Geo<N>::PPX, T = Geo<N>::TX;
-        const dim3 gx((N + 2 * P - 1) / (2 * P), a.d == 3 ? N : 1);
-        if (a.emb) {
-            if (hint) k_x_r2c_emb<N, NT_P1><<<gx, T, 0, s>>>(a.rho, X1, tw, ext);
-            else k_x_r2c_emb<N, 0><<<gx, T, 0, s>>>(a.rho, X1, tw, ext);
-        } else {
-            return launch_x_forward_v<P>(a, s);
-        }
+        return launch_x_forward_v<Geo<N>::PPX>(a, s);
     }
-    return hipGetLastError();
 }
 
 // Padding to B_3 on a cubic transform grid (lengths 3n/2): P1 and P5 with the density and the
 // potential at their own extents (a.px, a.py, a.pz), at the default tile.
-template <bool HV = false>
+template <int N, bool HV = false>
 static hipError_t launch_x_emb(const EvalArgs& a, hipStream_t s, int pass) {
-    constexpr int N = GS_N;
     if constexpr (N % 3 == 0) {
         using Gm = Geo<N>;
         Ext ext;
@@ -154,7 +136,19 @@ static hipError_t launch_x_emb(const EvalArgs& a, hipStream_t s, int pass) {
         const cpx* const tw = reinterpret_cast<const cpx*>(a.tw);
         dim3 gx((N + 2 * Gm::PPX - 1) / (2 * Gm::PPX), a.d == 3 ? N : 1);
         if (pass == 1) {
-            return launch_x_forward_split<p1_split_px<N>(3)>(a, s);
+            constexpr int PX1 = p1_split_px<N>(3);
+            cpx* const X1w = reinterpret_cast<cpx*>(a.X1);
+            const bool nt = a.hint_bits & 1;
+            if constexpr (PX1 > 0) {
+                constexpr int T1 = 2 * PX1 * Gm::G;
+                gx.x = (N + 2 * PX1 - 1) / (2 * PX1);
+                if (nt) k_x_r2c_emb_split<N, NT_P1, PX1><<<gx, T1, 0, s>>>(a.rho, X1w, tw, ext);
+                else k_x_r2c_emb_split<N, 0, PX1><<<gx, T1, 0, s>>>(a.rho, X1w, tw, ext);
+            } else {
+                if (nt) k_x_r2c_emb<N, NT_P1><<<gx, Gm::TX, 0, s>>>(a.rho, X1w, tw, ext);
+                else k_x_r2c_emb<N, 0><<<gx, Gm::TX, 0, s>>>(a.rho, X1w, tw, ext);
+            }
+            return hipGetLastError();
         }
         const cpx* const X1 = reinterpret_cast<const cpx*>(HV ? a.X2 : a.X1);
         constexpr int T = p5_threads<N, Gm::PPX>();
@@ -185,7 +179,7 @@ static hipError_t launch_x_emb(const EvalArgs& a, hipStream_t s, int pass) {
 // pairs per block; bits 6-7 then do not apply) where one is compiled.
 static hipError_t launch_x_inverse(const EvalArgs& a, hipStream_t s) {
     constexpr int N = GS_N;
-    if (a.emb) return launch_x_emb(a, s, 5);
+    if (a.emb) return launch_x_emb<N>(a, s, 5);
     if constexpr (x_radix_variant<N>()) {
         if ((a.tile_bits >> 10) & 1) return launch_x_inverse_v<Geo<N>::PPX, 1>(a, s);
     }
@@ -197,7 +191,7 @@ static hipError_t launch_x_inverse(const EvalArgs& a, hipStream_t s) {
 // Tile bit 9: the x-forward pass's radix-plan variant, as bit 10 for the x-inverse pass.
 static hipError_t launch_x_forward(const EvalArgs& a, hipStream_t s) {
     constexpr int N = GS_N;
-    if (a.emb) return launch_x_emb(a, s, 1);
+    if (a.emb) return launch_x_emb<N>(a, s, 1);
     if constexpr (x_radix_variant<N>()) {
         if ((a.tile_bits >> 9) & 1) return launch_x_forward_v<Geo<N>::PPX, 1>(a, s);
     }
@@ -267,10 +261,9 @@ static hipError_t launch_fused_v(const EvalArgs& a, hipStream_t s, const DipoleA
       if (a.d == 3) {
         cpx* const X2 = reinterpret_cast<cpx*>(a.X2);
         static const int cap3 = resident_blocks((const void*)k_fused<N, 3, SPEC_PLAIN, 0, PZ, false, RV>, T);
-        const int capf = a.max_blocks_fused > 0 ? a.max_blocks_fused : cap3;
         const int np = a.kxn * 2 * N;
         const int groups = (np + PZ - 1) / PZ;
-        const unsigned nb = gs_fused_persistent(3, N, a.dipolar) ? fused_grid(groups, capf, a.fused_grid_mult) : (unsigned)groups;
+        const unsigned nb = gs_fused_persistent(3, N, a.dipolar) ? fused_grid(groups, cap3, a.fused_grid_mult) : (unsigned)groups;
         if constexpr (ETILE) {
             if (a.energy) {
                 // with the energy sum of every pencil (the default tile only)
@@ -329,7 +322,7 @@ static hipError_t launch_plane(const EvalArgs& a, hipStream_t s, const DipoleArg
     constexpr int N = GS_N;
     if constexpr (plane_fused<N>()) {
         if (which == PASS_X_INVERSE_HALVES) {
-            if (a.emb) return launch_x_emb<true>(a, s, 5);
+            if (a.emb) return launch_x_emb<N, true>(a, s, 5);
             return launch_x_inverse_v<px_of<N>(0), 0, true>(a, s);
         }
         const cpx* const X1 = reinterpret_cast<const cpx*>(a.X1);
@@ -518,8 +511,10 @@ hipError_t GS_CAT(launch_eval_g_, GS_N)(const EvalArgs& a, hipStream_t s, int pa
             if (pass == 2 || pass == 4)
                 return ext.nz % Gm::PPY == 0 ? launch_y_g<N, true>(a, s, pass, ext) : launch_y_g<N, false>(a, s, pass, ext);
             if (pass != 3) return hipErrorInvalidValue;
-            return (2 * ext.ny) % Gm::PPZ == 0 ? launch_fused_g<N, 3, true>(a, s, ext, dip)
-                                               : launch_fused_g<N, 3, false>(a, s, ext, dip);
+            // every length is a multiple of 4, so groups of up to 8 of the 2 ny pencils are full
+            if constexpr (Gm::PPZ > 8)
+                if ((2 * ext.ny) % Gm::PPZ != 0) return launch_fused_g<N, 3, false>(a, s, ext, dip);
+            return launch_fused_g<N, 3, true>(a, s, ext, dip);
         }
     }
     if (pass != 3 || a.d != 2) return hipErrorInvalidValue;

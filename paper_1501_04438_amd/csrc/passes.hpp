@@ -258,7 +258,8 @@ template <int N, int PY> __host__ __device__ __forceinline__ int y_tile_of(int b
 
 // At n = 2048 the compiler's own allocation takes 256 VGPRs + 42 accumulator registers (one wave
 // per SIMD); capped at two waves per SIMD it spills 172 bytes per lane and still runs faster
-// (measured 0.038 -> 0.033 ms for 2D 2048^2; the same cap slows the x-inverse and n = 1024).
+// (measured 0.038 -> 0.033 ms for 2D 2048^2; the same cap slows the x-inverse and n = 1024).  At
+// that length this kernel runs as a tile variant only: the default is k_x_r2c_split.
 template <int N, int NT = NT_P1, int PX = Geo<N>::PPX, int XV = 0>
 __global__ void __launch_bounds__((PX * GeoX<N, XV>::G)) __attribute__((amdgpu_waves_per_eu(N == 2048 ? 2 : 1)))
 k_x_r2c(const double* __restrict__ rho, cpx* __restrict__ X1,
@@ -566,7 +567,7 @@ __global__ void __launch_bounds__((2 * PX * Geo<N>::G)) k_x_r2c_emb_split(const 
 // the first points of each axis) read, and the potential written, in place of copies into and
 // out of a grid-sized array.
 template <int N, int NT>
-__global__ void __launch_bounds__(Geo<N>::TX) __attribute__((amdgpu_waves_per_eu(N == 2048 ? 2 : 1)))
+__global__ void __launch_bounds__(Geo<N>::TX)
 k_x_r2c_emb(const double* __restrict__ rho, cpx* __restrict__ X1, const cpx* __restrict__ tw, Ext ext) {
     __shared__ cpx lds[Geo<N>::PPX * Geo<N>::A];
     x_r2c_tile<N, NT, true, Geo<N>::PPX, 0, true>((gp<const double>)rho, (gp<cpx>)X1, (gp<const cpx>)tw,

@@ -1,6 +1,7 @@
 """The rules that choose a pass's form, read from the compiled sources by a host program."""
 
 import os
+import re
 import shutil
 import subprocess
 
@@ -59,3 +60,19 @@ def test_runs_of_a_die(rules):
     tiles that share lines."""
     runs = {int(r[1]): (int(r[2]), int(r[3])) for r in rules if r[0] == "runs"}
     assert runs[320] == (5, 5) and runs[512] == (8, 8) and runs[256] == (2, 2) and runs[128] == (1, 1)
+
+
+def test_only_kernels_that_are_launched():
+    """Padding to B_3 transforms lengths 3 n / 2 at one tile per length; the fused pass's 3D groups of up
+    to 8 pencils are always full (every length is a multiple of 4)."""
+    lib = os.path.join(os.path.dirname(HERE), "paper_1501_04438_amd", "libgs.so")
+    if not os.path.exists(lib):
+        pytest.skip("library not built")
+    with open(lib, "rb") as f:
+        data = f.read()
+    emb = {tuple(m) for m in re.findall(rb"k_x_(r2c|c2r)_emb(?:_split)?ILi(\d+)E", data)}
+    assert emb and all(int(n) % 3 == 0 for _, n in emb)
+    tiles = set(re.findall(rb"k_x_r2c_emb_splitILi(\d+)ELi[01]ELi(\d+)E", data))
+    assert tiles and len(tiles) == len({n for n, _ in tiles})
+    ragged = {int(n) for n in re.findall(rb"k_fused_gILi(\d+)ELi3ELi[01]ELi[01]ELb[01]ELb0E", data)}
+    assert ragged and max(ragged) < 64
