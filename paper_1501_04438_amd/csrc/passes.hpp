@@ -695,10 +695,11 @@ __global__ void __launch_bounds__((PY * GeoX<N, YV>::G)) k_y_inv(const cpx* __re
 // P4 of a cubic grid with the two halves of the padded inverse on the two 32-lane halves of every
 // wave (as x_c2r_tile_split): each thread loads and transforms one half, and the halves' sums are
 // formed by a lane swap, each lane storing half of the pencil's values.  The same sums as
-// y_inv_tile, so the same bits.  Taken at n = 96, whose pass is too short for its waves to hide
-// a chain of two transforms (alone 9.97 -> 8.96, the evaluation 52.7 -> 51.4 us); at 80 the
-// evaluation takes 42.7 us with it and 40.4 without, from 112 on the pass takes the same time.
-template <int N> constexpr bool p4_split() { return N > 80 && N < 112; }
+// y_inv_tile, so the same bits.  Taken between the lengths whose middle passes are one launch (64)
+// and 128 where a thread holds few values (96: 12), whose pass is too short for its waves to hide a
+// chain of two transforms (alone 9.97 -> 8.96, the evaluation 52.7 -> 51.4 us); with 20 values (80) the
+// evaluation takes 42.7 us with it and 40.4 without, with 28 (112) and from 128 on the same time.
+template <int N> constexpr bool p4_split() { return N > 64 && N < 128 && Geo<N>::E <= 12; }
 template <int N, int NT, int PY>
 __device__ __forceinline__ void y_inv_tile_split(gp<const cpx> __restrict__ X2, gp<cpx> __restrict__ X1,
                                                  gp<const cpx> __restrict__ tw, int kx0, int bx, int kxl, int tid,
