@@ -359,7 +359,7 @@ def main() -> int:
     torch.cuda.synchronize()
 
     K = args.steps
-    steps = plan.steps()                       # pass id of every launch of one evaluation
+    steps = plan.steps()                       # pass id of every step of one evaluation
     S = len(steps)
     # HIP events without the system-scope fence (a timing-only event; with the fence every
     # record writes back and invalidates the caches), recorded by the library on the stream
@@ -554,7 +554,7 @@ def graph_figures(gs, torch, reps: int = 200):
         ue = u.clone()
         ms_graph = timed(g.replay)
         res[f"{kernel}_{n}"] = {"ms_eager": round(ms_eager, 5), "ms_graph": round(ms_graph, 5),
-                                "launches": len(plan.steps()), "same_bits": bool(torch.equal(u, ue))}
+                                "steps": len(plan.steps()), "same_bits": bool(torch.equal(u, ue))}
         del g
         plan.close()
     return res

@@ -164,8 +164,9 @@ typedef struct {
                                 GS_PLAN_AUTOTUNE picks them by timing            */
     int launch_hints;        /* 1 + the cache-hint bits of the passes (bit p-1 set: pass p
                                 uses its non-temporal hint variant, gs_plan_info.hint_bits);
-                                0 = the default for the grid's size.  Every value gives the same bits;
-                                GS_PLAN_AUTOTUNE picks them by timing            */
+                                0 = the default for the grid's and the slabs' size.  Every value
+                                gives the same bits; one launch of several passes takes none
+                                (gs_eval).  GS_PLAN_AUTOTUNE picks them by timing */
 } gs_options;
 
 typedef struct {
@@ -367,7 +368,8 @@ gs_status gs_eval_backward(gs_plan p, const double* grad_u_dev, double* grad_rho
  *                       the first gs_batch_eval (as graph replays when use_graph
  *                       is set) and cached in the process and,
  *                       if the environment variable GS_AUTOTUNE_CACHE names a
- *                       file, in that JSON file across processes.
+ *                       file, in that JSON file across processes (of this build
+ *                       of the library: other builds' choices are not taken).
  */
 typedef enum {
     GS_SCHED_AUTO = 0,
@@ -480,7 +482,9 @@ gs_status gs_eval_events(gs_plan p, const double* rho_dev, double* u_dev, void* 
  * passes one at a time: which = 1 workspace X1 ((n+1) n^(d-1) complex, layout
  * [z][kx][y] / [kx][y]), 2 workspace X2 (3D: [kx - kx0][ky][z] of the last slab),
  * 3 the stored spectrum octant ((n+1)^d FP64).  X2 holds one kx slab:
- * 2n n (slab_planes) complex values.  to_device = 0 reads into host,
+ * 2n n (slab_planes) complex values.  The layouts are those of single steps
+ * (gs_eval_step); after a gs_eval that runs the middle passes in one launch, X1 is
+ * pass 1's and X2 holds two halves of pass 4's result.  to_device = 0 reads into host,
  * 1 writes from host.  count is in doubles and must equal the buffer size.
  * Synchronises the plan's stream. */
 gs_status gs_plan_buffer(gs_plan p, int which, int to_device, double* host, size_t count);

@@ -65,13 +65,15 @@ class Plan:
             (Ly, Lx)) for a rectangular box or grid (Section 2.5)
     eps:    Gaussian-sum accuracy; delta_rel: near-field radius / max L (below min L / max L)
     dipole: (n_vec, m_vec) for "dipolar3d"; custom: (w, tau) for "gaussian_sum"
-    autotune: time the launch variants (cache hints per pass, fused-pass grid, tile shapes,
-              the fused pass's radix plan) at plan creation and keep the fastest (cached per
-              device and size; the results are bitwise the same for every variant but the
-              radix plan, which agrees to rounding and is kept only when 1 % faster)
-    tile_variants: tile shapes of the cubic passes and, bit 8, the fused pass's radix-plan
-        variant (gs_options.tile_variants bits; 0 = defaults)
-    hint_bits: cache-hint variants of the passes (bit p-1: pass p non-temporal; None = defaults)
+    autotune: time the launch variants (cache hints per pass, rounds of the fused pass, tile
+              shapes, the radix plans of the passes) at plan creation and keep the fastest (cached
+              per device, build of the library and size; the results are bitwise the same for every
+              variant but the radix plans, which agree to rounding and are kept only when 1 %
+              faster)
+    tile_variants: tile shapes of the cubic passes and, bits 8 to 12, radix-plan variants
+        (gs_options.tile_variants bits; 0 = defaults)
+    hint_bits: cache-hint variants of the passes (bit p-1: pass p non-temporal; None = the default
+        for the size of the grid and of its slabs)
     workspace: False creates the plan without an evaluation workspace of its own; it is
               then evaluated with eval_static only
     laplacian: "padded" (default) or "unpadded": the grid on which the near-field Taylor term
@@ -304,7 +306,8 @@ class Plan:
         return g
 
     def steps(self) -> list[int]:
-        """Pass id of every kernel launch of one evaluation, in order."""
+        """Pass id of every step of one evaluation, in order (one launch each in eval_step and
+        eval_events; eval joins the three middle steps of cubes up to 64^3 in one launch)."""
         c = lib().gs_plan_steps(self._h, None, 0)
         buf = (C.c_int * max(c, 1))()
         lib().gs_plan_steps(self._h, buf, c)

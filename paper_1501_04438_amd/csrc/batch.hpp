@@ -234,7 +234,8 @@ __global__ void __launch_bounds__(BATCH_THREADS) k_batch_size(const BatchProblem
 // observing the counter.  (At agent scope, sc1: the workgroup-scope form, sc0, leaves lines of
 // this CU's L1 that other CUs have since written; seen as stale values in a kernel that rewrote a
 // small buffer at short intervals.  A batch of 20 problems up to 128^3:
-// queue 944 -> 958 us.)
+// queue 944 -> 958 us; with the tiles of now, 64 problems of 32^3 (twice the tasks) 192 -> 237 us,
+// where the schedule that the tuner takes needs 127.)
 // Otherwise agent-scope release (L2 write-back) and acquire (L2 invalidate).
 //
 // A dependency wait gives up after spin_limit polls (far beyond any task's

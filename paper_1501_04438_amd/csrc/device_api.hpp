@@ -26,13 +26,14 @@ struct EvalArgs {
     double nm_over_M = 0.0;
     int kx0 = 0, kxn = 0;             // 3D passes 2-4: the kx slab [kx0, kx0 + kxn); X2 holds the slab
     // Launch variants (none changes a single bit of the result): bit p-1 clear selects
-    // plain (cached) memory accesses for pass p instead of its cache-hint default;
-    // fused_grid_mult = rounds of co-resident blocks in the persistent fused pass (3D; the 2D
-    // fused pass runs one block per pencil group).
+    // plain (cached) memory accesses for pass p instead of its cache-hint variant;
+    // fused_grid_mult = rounds of co-resident blocks of the fused pass where it is persistent
+    // (3D; sizes.hpp).
     int hint_bits = 27;
     int fused_grid_mult = 4;
-    // Tile shapes of the cubic passes (bits 0-1 x passes, 2-3 y passes, 4-5 fused pass; 0 =
-    // compiled defaults; see eval_instance.hip); the same bits for every value.
+    // Tile shapes of the cubic passes (bits 0-1 x-forward, 2-3 y passes, 4-5 fused, 6-7 x-inverse
+    // pass; 0 = compiled defaults; the same results bit for bit) and, bits 8 to 12, radix-plan
+    // variants (the same to rounding); see eval_instance.hip.
     int tile_bits = 0;
     // Energy (when energy != nullptr): E = escale * sum_i rho_i u_i, summed in the fused pass
     // by Parseval's identity, one partial per pencil in epart (epencils of them, then room for
@@ -87,8 +88,8 @@ hipError_t launch_eval(const EvalArgs& a, hipStream_t s, int which = -1);
 constexpr int PASS_PLANE = 6, PASS_X_INVERSE_HALVES = 7;
 bool plane_fused(int n);
 bool eval_size_supported(int d, int n);
-// Tile variants compiled for length n: bit 0 x double, 1 y half, 2 y double, 3 fused half,
-// 4 fused double.
+// Variants compiled for length n: bit 0 x double, 1 y half, 2 y double, 3 fused half, 4 fused
+// double; radix plans: 5 fused, 6 x passes, 7 y passes.
 int tile_variants(int n);
 int eval_sizes(int d, long long* out, int cap);
 

@@ -34,7 +34,9 @@ static int resident_blocks(const void* fn, int threads) {
 // many), y passes bits 2-3 (0: default z-pencils per block, 1: half, 2: twice), fused pass
 // bits 4-5 (0: default pencils per block, 1: half, 2: twice), x-inverse pass bits 6-7 (as
 // the x-forward pass).  Compiled for the lengths gs_tile_variants
-// names, where LDS allows; elsewhere every value selects the default.
+// names, where LDS allows; elsewhere every value selects the default.  Bits 8 to 12 select
+// radix-plan variants (fused, x-forward, x-inverse, y-forward, y-inverse pass), which round
+// differently.
 constexpr int LDS_LIMIT = 160 * 1024;
 template <int N> constexpr int px_of(int v) {
     constexpr int P = Geo<N>::PPX;
@@ -248,8 +250,8 @@ static hipError_t launch_y(const EvalArgs& a, hipStream_t s, int pass) {
     return launch_y_v<py_of<N>(0)>(a, s, pass);
 }
 
-// Fused pass with PZ pencils per block on radix plan RV (3D: persistent rounds at n = 256;
-// 2D: one block per pencil group).  The energy instances exist for each plan's default tile.
+// Fused pass with PZ pencils per block on radix plan RV (3D: persistent rounds where
+// gs_fused_persistent says so; 2D: one block per pencil group).  The energy instances exist for each plan's default tile.
 template <int PZ, int RV = 0>
 static hipError_t launch_fused_v(const EvalArgs& a, hipStream_t s, const DipoleArgs& dip) {
     constexpr int N = GS_N;

@@ -51,8 +51,8 @@ template <bool NT, class T> __device__ __forceinline__ void stg(gp<T> p, T v) {
     else *p = v;
 }
 // Each pass is compiled with these hints and without (plain accesses); the launch picks per
-// pass (hint bits of the plan, default: hints for P1, P2, P4, P5 and plain P3, chosen by
-// measurement at n = 256 over whole five-pass chains): non-temporal loads where the input is
+// pass (hint bits of the plan; the default goes by the size of X2: none, P4 and P5, or all but P3,
+// see default_hints in gs_api.cpp): non-temporal loads where the input is
 // streamed once (P1, P4; P3's variant), non-temporal stores where the output is scattered in
 // short runs (P2) or real (P5); P5 keeps its loads cached because each Hermitian row is read
 // twice (direct and mirrored), and the fused pass its spectrum loads, because the +ky and
@@ -138,7 +138,7 @@ template <int N, int PX> constexpr int line_tiles() {
 // instead of every eighth 128-byte line (`part` tiles, the ones that share lines, at least).
 // Measured x passes and y passes together, plain order -> this: 320^3 1652 -> 1616, 384^3 2847 ->
 // 2777, 512^3 6160 -> 5879 us; at 128^3 to 192^3 the same time within 1 %, in 2D (2048^2) 2.5 % slower.
-// At 256 two tiles a run: 615.7 -> 611.5 us.
+// At 256 two tiles a run: 618.2 -> 610.8, dipolar 644.0 -> 640.2 us (best of six runs a side in turn).
 template <int N> constexpr int die_run(int tiles, int part) {
     constexpr int least = N == 256 ? 2 : 1;
     return N >= 320 && tiles / 8 > part ? tiles / 8 : part > least ? part : least;
@@ -1155,9 +1155,10 @@ k_fused(cpx* __restrict__ Xg, const double* __restrict__ specg,
 // y-inverse's result, H[hy][z][kx][y], which the x-inverse pass adds as it loads.
 //
 // The same transforms on the same plans as the three passes, and the halves are added in their
-// order: the same bits.  What it saves is two launches and the trips of X2 through memory
-// (64 (n+1) n^2 bytes), which at these sizes are latency: every pass is a kernel of 3 to 6 us of
-// which the data's share is below 1 us.
+// order: the same bits.  What it saves is two launches and the four trips of X2 (two stores, two
+// loads, 128 (n+1) n^2 bytes), which at these sizes are latency: every pass is a kernel of 3 to 6 us of
+// which the data's share is below 1 us.  What it costs is X1 read by both blocks of a plane (on one
+// die) and 16 (n+1) n^2 bytes more written and read again by the x-inverse pass (two halves).
 // Layout of the LDS: row ky (of n) at ky * 2 AZ, the two exchange areas of its z pencil, so a
 // pencil's row is read and written by its own wave only; the y transforms' areas (A slots each,
 // the G <= 8 threads of a transform inside one wave) overlap the rows, block barriers between.

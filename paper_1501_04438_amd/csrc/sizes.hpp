@@ -18,7 +18,7 @@ constexpr bool gs_fused_persistent(int d, int n, bool dipolar) {
 }
 // The same on grids whose axes differ, by the length n of the fused axis: always, never, or where
 // the pass's array X2 (a slab's planes) is larger than the 256 MB cache (with the energy's sums,
-// whose kernel has two waves either way, from 190 MB).  Whole evaluations (z
+// whose kernel gives up one wave of three for the loop, from 190 MB).  Whole evaluations (z
 // first), one block per group -> persistent:
 //   plain: 128x256x512 648 -> 634, 512x256x128 698 -> 661, 384x256x320 1570 -> 1470, 256x192x320 637
 //   -> 612, 128x256x192 243 -> 238; 192x128x160 156 -> 158 (energy 170 -> 166); but 224x320x192 (28
